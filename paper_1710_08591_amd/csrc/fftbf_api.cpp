@@ -26,6 +26,7 @@ struct bf_plan {
   int32_t* even = nullptr; // cyclic co-adding: [n_chan][m_ns] = 2 A (the even padded outputs)
   double* dl = nullptr;    // [n_chan][2]
   void* mix = nullptr;     // mixed-precision operand tables
+  double2* lag = nullptr;  // FP64 twiddles of the stacked-visibility transform
 };
 
 namespace {
@@ -59,6 +60,7 @@ void free_plan(bf_plan* p) {
   if (p->even) (void)hipFree(p->even);
   if (p->dl) (void)hipFree(p->dl);
   if (p->mix) (void)hipFree(p->mix);
+  if (p->lag) (void)hipFree(p->lag);
   delete p;
 }
 
@@ -187,6 +189,10 @@ bf_status bf_plan_create(const bf_plan_desc* desc, bf_plan** plan) {
     e = hipMalloc(&p->dl, sizeof(double) * dl.size());
     if (e == hipSuccess) e = hipMemcpyAsync(p->dl, dl.data(), sizeof(double) * dl.size(), hipMemcpyHostToDevice, s);
   }
+  if (e == hipSuccess && d.m_ew == 4 && !folded) {
+    e = hipMalloc(&p->lag, fftbf::lag_table_bytes(d.n_ns));
+    if (e == hipSuccess) e = fftbf::launch_lag_table(p->lag, d.n_ns, s);
+  }
   if (e == hipSuccess && d.precision != BF_PREC_FP32) {
     e = hipMalloc(&p->mix, fftbf::mix_table_bytes(d.n_ns, d.precision));
     if (e == hipSuccess) e = fftbf::launch_mix_tables(p->mix, d.n_ns, d.precision, s);
@@ -252,7 +258,23 @@ static bf_status beamform_fft_impl(const bf_plan* plan, const uint8_t* volts, in
   const int64_t n_wg = n_blk * d.n_chan * n_pg;
   if (n_wg > 0x7FFFFFFFLL) return fail(BF_ERR_UNSUPPORTED, "beamform_fft: grid too large, split the call");
   hipError_t e;
-  if (d.precision == BF_PREC_FP32) {
+  const int pol_iter = (n_pg == 1) ? d.n_pol : 1;
+  if (kind == BF_OUT_INTENSITY && !taper && plan->lag) {
+    fftbf::LagArgs a{};
+    a.volts = reinterpret_cast<const uint32_t*>(volts);
+    a.n_task = n_wg;
+    a.n_chan = d.n_chan;
+    a.n_pol = d.n_pol;
+    a.n_pg = n_pg;
+    a.pol_iter = pol_iter;
+    a.block = d.block;
+    a.tw = plan->lag;
+    a.sel = plan->sel;
+    a.n_keep = keep_of(d);
+    a.out = static_cast<float*>(out);
+    a.norm = 1.0f / float(d.n_ew * d.n_ns);
+    e = fftbf::launch_lag(a, d.n_ns, s);
+  } else if (d.precision == BF_PREC_FP32) {
     fftbf::Fft32Args a{};
     a.volts = reinterpret_cast<const uint32_t*>(volts);
     a.n_time = n_time;

@@ -50,6 +50,24 @@ hipError_t launch_fft32(const Fft32Args& a, int n_ns, int taper, bool cplx, int6
                         hipStream_t s);
 bool fft32_fuses_ew8(int n_ns, int taper, bool cplx, int fold);
 
+// unwindowed intensities through redundancy-stacked visibilities (k_lag.hip)
+struct LagArgs {
+  const uint32_t* volts;   // frames as dwords: [t][chan][pol][n_ns] (4 E-W bytes each)
+  int64_t n_task;          // (block, channel, polarisation group) tasks
+  int n_chan, n_pol, n_pg, pol_iter, block;
+  const double2* tw;       // launch_lag_table's twiddles
+  const int32_t* sel;      // [n_chan][n_keep] or null (identity)
+  int n_keep;
+  float* out;
+  float norm;              // 1 / (n_ew n_ns)
+  int tpi, iters;          // tasks per round and rounds of a workgroup's unit (set by the launch)
+};
+// doubles pairs of the twiddle table of an m-point transform
+constexpr int lag_tw_count(int m) { return 7 * (m / 8) + (m > 64 ? 7 * (m / 64) : 0); }
+size_t lag_table_bytes(int n_ns);
+hipError_t launch_lag_table(double2* tw, int n_ns, hipStream_t s);
+hipError_t launch_lag(const LagArgs& a, int n_ns, hipStream_t s);
+
 // FP64 table generation on the device
 int twiddle_mult_count(int g, int l2);
 hipError_t launch_twiddle_table(float2* tw, float* mult, int g, int l2, int m, hipStream_t s);
