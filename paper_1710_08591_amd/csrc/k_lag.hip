@@ -37,14 +37,13 @@
 // within 3 % of each other.
 #include <type_traits>
 
+#include "dev_bytes.h"
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace fftbf {
 
 namespace {
-
-typedef int v4i __attribute__((ext_vector_type(4)));
 
 struct cd {
   double r, i;
@@ -93,14 +92,6 @@ __device__ __forceinline__ void dft_n(cd* x) {
   else if constexpr (R == 2) dft2(x);
 }
 
-// a wavefront's LDS operations execute in the order it issues them, so data
-// that stays within one wavefront needs the compiler's order only
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // E-W 4-point transform of four samples of one N-S position (dwords w0 .. w3:
 // byte q holds antenna q, real part in its high nibble), four samples per
 // register: y[2 e + part], byte t = sample t, int8.  A byte lane of a word
@@ -108,13 +99,8 @@ __device__ __forceinline__ void wave_sync() {
 // exact as long as the digits end in [0, 255], so the digits carry a bias,
 // 128 at the end, where flipping the top bit leaves the signed byte.
 __device__ __forceinline__ void ew_transform4(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t* y) {
-  const uint32_t a01 = __builtin_amdgcn_perm(w1, w0, 0x05010400u), b01 = __builtin_amdgcn_perm(w1, w0, 0x07030602u);
-  const uint32_t a23 = __builtin_amdgcn_perm(w3, w2, 0x05010400u), b23 = __builtin_amdgcn_perm(w3, w2, 0x07030602u);
   uint32_t q[4];
-  q[0] = __builtin_amdgcn_perm(a23, a01, 0x05040100u);
-  q[1] = __builtin_amdgcn_perm(a23, a01, 0x07060302u);
-  q[2] = __builtin_amdgcn_perm(b23, b01, 0x05040100u);
-  q[3] = __builtin_amdgcn_perm(b23, b01, 0x07060302u);
+  transpose_bytes(w0, w1, w2, w3, q);
   constexpr uint32_t kM = 0x0F0F0F0Fu, kB = 0x08080808u;
   uint32_t s02p[2], s02m[2], s13[2], d02[2], d13[2];
 #pragma unroll
@@ -146,11 +132,6 @@ __device__ __forceinline__ void ew_transform4(uint32_t w0, uint32_t w1, uint32_t
 // two, fits int32 whatever the voltages are: |x|^2 <= 2 * 32^2 per antenna
 // and sample, so 2 * 2^11 * count <= 2^31.
 constexpr int kLagLimit = 1 << 19;
-
-// the negatives of four int8 in [-127, 127]
-__device__ __forceinline__ int neg_bytes(int z) {
-  return (int)((((uint32_t)z ^ 0x7F7F7F7Fu) + 0x01010101u) ^ 0x80808080u);
-}
 
 // One workgroup: four wavefronts, wavefront e owns E-W beam e.  256 / N tasks
 // (block, channel, polarisation group) at a time, two rounds per output.

@@ -120,34 +120,18 @@ __global__ __launch_bounds__(64) void k_tied(TiedArgs a) {
   }
 }
 
-// Voltage variant for the 4 x 16 lattice (M_ns = 32): per group of 16
-// samples the wave forms the 4 x 32 FFT beams of each sample in LDS (lane =
-// (sample, E-W beam): two signed 4-bit dot products per N-S position for the
-// E-W DFT, then the zero-padded 32-point N-S DFT in registers), then every
-// lane interpolates its own pointing from LDS broadcasts.
+// Windowed voltage variant for the 4 x 16 lattice (M_ns = 32; unwindowed
+// voltages take k_tied_lag): per group of 16 samples the wave forms the
+// 4 x 32 FFT beams of each sample in LDS (lane = (sample, E-W beam): the
+// weighted E-W DFT, then the zero-padded 32-point N-S DFT in registers), then
+// every lane interpolates its own pointing from LDS broadcasts.
 constexpr int kV16N = 16, kV16M = 32, kV16TS = 16;
 
 struct V16Lane {
-  int ts, e, wre, wim;
+  int ts, e;
 };
 
-__device__ __forceinline__ V16Lane v16_lane(int lane) {
-  V16Lane l;
-  l.ts = lane >> 2;
-  l.e = lane & 3;
-  l.wre = 0;
-  l.wim = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int k = (l.e * q) & 3;
-    const int sr = 4 * (2 * q + 1), si = 4 * (2 * q);
-    if (k == 0) { l.wre |= 1 << sr;   l.wim |= 1 << si; }
-    if (k == 1) { l.wre |= 1 << si;   l.wim |= 0xF << sr; }
-    if (k == 2) { l.wre |= 0xF << sr; l.wim |= 0xF << si; }
-    if (k == 3) { l.wre |= 0xF << si; l.wim |= 1 << sr; }
-  }
-  return l;
-}
+__device__ __forceinline__ V16Lane v16_lane(int lane) { return {lane >> 2, lane & 3}; }
 
 // The interpolation of a group of 16 samples runs on the FP16 matrix cores
 // (v_mfma_f32_16x16x32_f16) with two-term operands:
@@ -202,7 +186,6 @@ __device__ __forceinline__ int b16_chunk(int term, int kb, int g, int s) {
   return ((term * 8 + kb) * 4 + g) * 16 + s;
 }
 
-template <bool TAPER>
 __device__ __forceinline__ void v16_fft_to_lds(const uint32_t (&dw)[kV16N], const V16Lane& l,
                                                const float* lds_h, _Float16* lds_g, int ds) {
   constexpr int N = kV16N, MNS = kV16M;
@@ -210,24 +193,20 @@ __device__ __forceinline__ void v16_fft_to_lds(const uint32_t (&dw)[kV16N], cons
 #pragma unroll
   for (int j = 0; j < N; ++j) {
     const uint32_t d = dw[j];
-    if constexpr (TAPER) {
-      float re = 0.f, im = 0.f;
+    float re = 0.f, im = 0.f;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int k = (l.e * q) & 3;
-        const float h = lds_h[j * 4 + q];
-        const float xr = (float)(int)__builtin_amdgcn_sbfe((int)d, 8 * q + 4, 4) * h;
-        const float xi = (float)(int)__builtin_amdgcn_sbfe((int)d, 8 * q, 4) * h;
-        // x * (-i)^k
-        const float ur = (k == 0) ? xr : (k == 1) ? xi : (k == 2) ? -xr : -xi;
-        const float ui = (k == 0) ? xi : (k == 1) ? -xr : (k == 2) ? -xi : xr;
-        re += ur;
-        im += ui;
-      }
-      x[j] = cf{re, im};
-    } else {
-      x[j] = cf{(float)sdot8((int)d, l.wre), (float)sdot8((int)d, l.wim)};
+    for (int q = 0; q < 4; ++q) {
+      const int k = (l.e * q) & 3;
+      const float h = lds_h[j * 4 + q];
+      const float xr = (float)(int)__builtin_amdgcn_sbfe((int)d, 8 * q + 4, 4) * h;
+      const float xi = (float)(int)__builtin_amdgcn_sbfe((int)d, 8 * q, 4) * h;
+      // x * (-i)^k
+      const float ur = (k == 0) ? xr : (k == 1) ? xi : (k == 2) ? -xr : -xi;
+      const float ui = (k == 0) ? xi : (k == 1) ? -xr : (k == 2) ? -xi : xr;
+      re += ur;
+      im += ui;
     }
+    x[j] = cf{re, im};
   }
   cf y[MNS];
   padded_dft<N>(x, y);
@@ -542,10 +521,9 @@ __global__ __launch_bounds__(256) void k_tied_b16(TiedArgs a) {
 // wavefront waits while another forms beams.
 constexpr int kV16Buf = 2 * 8 * 4 * 16 * 8;          // FP16 values per group buffer (16 KB)
 
-template <bool TAPER>
 __global__ __launch_bounds__(256) void k_tied_v16(TiedArgs a) {
   __shared__ __attribute__((aligned(16))) _Float16 lds_b[4 * kV16Buf];
-  __shared__ float lds_h[TAPER ? kV16N * 4 : 1];
+  __shared__ float lds_h[kV16N * 4];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int n_ptile = (a.n_point + 63) / 64;
   const int n_pg = a.pol_sum ? 1 : a.n_pol;
@@ -559,19 +537,14 @@ __global__ __launch_bounds__(256) void k_tied_v16(TiedArgs a) {
   const bool wave_live = ptile * 64 + wave * 16 < a.n_point;
   const int pp = live ? p : a.n_point - 1;
 
-  if constexpr (TAPER) {
-    for (int i = tid; i < kV16N * 4; i += 256) lds_h[i] = a.taper[i];
-  }
+  for (int i = tid; i < kV16N * 4; i += 256) lds_h[i] = a.taper[i];
   TiedW w;
   if (wave_live) tied_weights(a.dl[2 * chan] * a.dircos[2 * pp], a.dl[2 * chan + 1] * a.dircos[2 * pp + 1], lane >> 4, w);
   const V16Lane l = v16_lane(lane);
   __syncthreads();
-  int ds = 8;
-  if constexpr (TAPER) {
-    float hmax = 0.f;
-    for (int i = 0; i < kV16N * 4; ++i) hmax = fmaxf(hmax, fabsf(lds_h[i]));
-    ds = v16_data_scale(hmax);
-  }
+  float hmax = 0.f;
+  for (int i = 0; i < kV16N * 4; ++i) hmax = fmaxf(hmax, fabsf(lds_h[i]));
+  const int ds = v16_data_scale(hmax);
   const float out_scale = ldexpf(1.f, -2 * (ds + kV16Wscale));
 
   const int pol_lo = a.pol_sum ? 0 : pg, pol_hi = a.pol_sum ? a.n_pol : pg + 1;
@@ -602,7 +575,7 @@ __global__ __launch_bounds__(256) void k_tied_v16(TiedArgs a) {
     float accg[4] = {0.f, 0.f, 0.f, 0.f};
     for (int pol = pol_lo; pol < pol_hi; ++pol) {
       const int64_t tw = tq + kV16TS * wave;
-      if (tw < t1) v16_fft_to_lds<TAPER>(nd, l, lds_h, lds_b + wave * kV16Buf, ds);
+      if (tw < t1) v16_fft_to_lds(nd, l, lds_h, lds_b + wave * kV16Buf, ds);
       __syncthreads();
       {
         // the next (quad, pol) of this wavefront, if any
@@ -639,89 +612,6 @@ __global__ __launch_bounds__(256) void k_tied_v16(TiedArgs a) {
         acc = 0.f;
         gcnt = 0;
         ++blk;
-      }
-    }
-  }
-}
-
-// Persistent tile worker of the tied-beam server: each workgroup takes tiles
-// (request, channel, 64 pointings, run of 16-sample blocks) from the batch,
-// reading voltages from the device ring (absolute sample s lives in slot
-// s mod ring_samples).  A tile's arithmetic is the same as k_tied_v16's (the
-// same quads of 16-sample groups) and does not depend on which other tiles
-// share the launch.
-__global__ __launch_bounds__(256) void k_serve(const ServeTile* __restrict__ tiles, int n_tiles,
-                                               const uint32_t* __restrict__ ring, int64_t ring_samples,
-                                               int n_chan, int n_pol, const double* __restrict__ dl) {
-  __shared__ __attribute__((aligned(16))) _Float16 lds_b[4 * kV16Buf];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const V16Lane l = v16_lane(lane);
-  const float out_scale = ldexpf(1.f, -2 * (8 + kV16Wscale));
-  const int64_t frame_dw = (int64_t)n_chan * n_pol * kV16N;
-  for (int ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
-    const ServeTile t = tiles[ti];
-    const int p = t.ptile * 64 + wave * 16 + (lane & 15);
-    const bool live = p < t.n_point;
-    const bool wave_live = t.ptile * 64 + wave * 16 < t.n_point;
-    const int pp = live ? p : t.n_point - 1;
-    TiedW w;
-    if (wave_live)
-      tied_weights(dl[2 * t.chan] * t.dircos[2 * pp], dl[2 * t.chan + 1] * t.dircos[2 * pp + 1], lane >> 4, w);
-    // ring slot of this wavefront's first sample (the same for every pol),
-    // advanced by a quad of groups per pass (the ring holds at least 16
-    // samples, so a lane's sample l.ts < 16 past it wraps at most once)
-    const int64_t sl0 = (t.t_start + (int64_t)(t.blk0 + wave) * kV16TS) % ring_samples;
-    auto frames = [&](int64_t sl, int pol) {
-      int64_t slot = sl + l.ts;
-      if (slot >= ring_samples) slot -= ring_samples;
-      return ring + slot * frame_dw + ((int64_t)t.chan * n_pol + pol) * kV16N;
-    };
-    // the next group's frames are loaded while the current quad is interpolated
-    uint32_t nd[kV16N];
-    if (wave < t.n_blk) {
-      v16_load(frames(sl0, 0), nd);
-    } else {
-#pragma unroll
-      for (int j = 0; j < kV16N; ++j) nd[j] = 0u;
-    }
-    for (int pol = 0; pol < n_pol; ++pol) {
-      int64_t sl = sl0;
-      for (int b0 = 0; b0 < t.n_blk; b0 += 4) {
-        if (b0 + wave < t.n_blk) v16_fft_to_lds<false>(nd, l, nullptr, lds_b + wave * kV16Buf, 8);
-        __syncthreads();
-        {
-          int64_t sn = sl + 4 * kV16TS;
-          while (sn >= ring_samples) sn -= ring_samples;
-          int bn = b0 + 4, pn = pol;
-          if (bn >= t.n_blk) {
-            bn = 0;
-            ++pn;
-            sn = sl0;
-          }
-          if (pn < n_pol && bn + wave < t.n_blk) {
-            v16_load(frames(sn, pn), nd);
-          } else {
-#pragma unroll
-            for (int j = 0; j < kV16N; ++j) nd[j] = 0u;
-          }
-        }
-        float accg[4] = {0.f, 0.f, 0.f, 0.f};
-        if (wave_live) {
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            if (b0 + g < t.n_blk) accg[g] = tied_block_mfma(lds_b + g * kV16Buf, w, lane) * out_scale;
-        }
-        __syncthreads();
-        if (live && lane < 16) {
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            if (b0 + g >= t.n_blk) break;
-            const int64_t ob = t.blk0 + b0 + g;
-            t.out[((ob * t.n_chan_req + (t.chan - t.chan_lo)) * n_pol + pol) * (int64_t)t.n_point + p] = accg[g];
-          }
-        }
-        sl += 4 * kV16TS;
-        while (sl >= ring_samples) sl -= ring_samples;
       }
     }
   }
@@ -898,24 +788,16 @@ hipError_t launch_tied(const TiedArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_serve(const ServeTile* tiles, int n_tiles, const uint32_t* ring, int64_t ring_samples,
-                        int n_chan, int n_pol, const double* dl, hipStream_t s) {
-  if (n_tiles <= 0) return hipSuccess;
-  const int grid = n_tiles < 8192 ? n_tiles : 8192;
-  hipLaunchKernelGGL(k_serve, dim3(grid), dim3(256), 0, s, tiles, n_tiles, ring, ring_samples, n_chan, n_pol, dl);
-  return hipGetLastError();
-}
-
 hipError_t launch_tied_v(const TiedArgs& a, hipStream_t s) {
   if (a.n_ns != 16 || a.m_ns != 32 || a.block % 16) return hipErrorNotSupported;
+  if (!a.taper) return launch_tied_lag(a, s);      // unwindowed: exact stacked visibilities
   const int n_ptile = (a.n_point + 63) / 64;
   const int64_t span = (int64_t)a.block * kTiedBlocksPerWg;
   const int64_t n_run = (a.n_time + span - 1) / span;
   const int n_pg = a.pol_sum ? 1 : a.n_pol;
   if ((int64_t)n_ptile * n_run > 0x7FFFFFFF || a.n_chan_sub > 65535) return hipErrorInvalidConfiguration;
   dim3 grid((unsigned)(n_ptile * n_run), (unsigned)a.n_chan_sub, (unsigned)n_pg);
-  if (a.taper) hipLaunchKernelGGL(k_tied_v16<true>, grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_tied_v16<false>, grid, dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_tied_v16, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -105,7 +105,9 @@ struct ServeTile {
 };
 hipError_t launch_serve(const ServeTile* tiles, int n_tiles, const uint32_t* ring, int64_t ring_samples,
                         int n_chan, int n_pol, const double* dl, hipStream_t s);
+// from voltages, 4 x 16 lattice, block a multiple of 16 (without a window: launch_tied_lag)
 hipError_t launch_tied_v(const TiedArgs& a, hipStream_t s);
+hipError_t launch_tied_lag(const TiedArgs& a, hipStream_t s);
 
 // intensity-domain regridding of FFT beams (N-S axis)
 struct RegridArgs {
