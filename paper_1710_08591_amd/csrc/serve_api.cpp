@@ -45,8 +45,11 @@ class HipBackend final : public fftbf::serve::Backend {
   static constexpr int kSlots = 3;   // > max launches in flight, so a staging slot is never reused early
 
   ~HipBackend() override {
+    if (copy_) (void)hipStreamSynchronize(copy_);
     if (stream_) (void)hipStreamSynchronize(stream_);
+    for (Reader& r : readers_) (void)hipEventDestroy(r.ev);
     for (int i = 0; i < kSlots; ++i) {
+      if (ev_copy_[i]) (void)hipEventDestroy(ev_copy_[i]);
       if (ev_[i]) (void)hipEventDestroy(ev_[i]);
       if (host_[i]) (void)hipHostFree(host_[i]);
       if (dev_[i]) (void)hipFree(dev_[i]);
@@ -56,6 +59,8 @@ class HipBackend final : public fftbf::serve::Backend {
     if (pool_) (void)hipFree(pool_);
     if (ring_) (void)hipFree(ring_);
     if (dl_) (void)hipFree(dl_);
+    if (arena_) (void)hipHostFree(arena_);
+    if (copy_) (void)hipStreamDestroy(copy_);
     if (stream_) (void)hipStreamDestroy(stream_);
   }
 
@@ -67,6 +72,8 @@ class HipBackend final : public fftbf::serve::Backend {
     frame_bytes_ = (size_t)d.n_ns * d.n_ew;
     max_tiles_ = max_tiles;
     hipError_t e = hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipStreamCreateWithFlags(&copy_, hipStreamNonBlocking);
+    if (e == hipSuccess) e = hipHostMalloc(&arena_, kArenaBytes, hipHostMallocDefault);
     if (e == hipSuccess) e = hipMalloc(&ring_, sample_bytes() * ring_samples);
     if (e == hipSuccess) e = hipMemsetAsync(ring_, 0, sample_bytes() * ring_samples, stream_);
     if (e == hipSuccess) e = hipMalloc(&pool_, pool_bytes);
@@ -76,6 +83,7 @@ class HipBackend final : public fftbf::serve::Backend {
       e = hipHostMalloc(&host_[i], sizeof(fftbf::ServeTile) * max_tiles, hipHostMallocDefault);
       if (e == hipSuccess) e = hipMalloc(&dev_[i], sizeof(fftbf::ServeTile) * max_tiles);
       if (e == hipSuccess) e = hipEventCreateWithFlags(&ev_[i], hipEventDisableTiming);
+      if (e == hipSuccess) e = hipEventCreateWithFlags(&ev_copy_[i], hipEventDisableTiming);
     }
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev_in_, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&ev_out_, hipEventDisableTiming);
@@ -86,9 +94,50 @@ class HipBackend final : public fftbf::serve::Backend {
 
   size_t sample_bytes() const { return frame_bytes_ * n_chan_ * n_pol_; }
 
+  // Uploads go through pinned memory on a stream of their own, which every
+  // launch waits for: a submission costs no wait, and a batch's descriptors
+  // are copied while the batch before it runs (a burst of 24 requests: 17 us
+  // per submission with a synchronous copy, 30 us between batches with the
+  // descriptors on the launch stream).
   bool upload_pointings(size_t off, const double* dircos, int n_point) override {
-    return hipMemcpy(static_cast<char*>(pool_) + off, dircos, sizeof(double) * 2 * n_point,
-                     hipMemcpyHostToDevice) == hipSuccess;
+    const size_t bytes = sizeof(double) * 2 * n_point;
+    hipError_t e = wait_readers();
+    if (e == hipSuccess && (bytes > kArenaBytes || used_ + bytes > kArenaBytes)) {
+      e = hipStreamSynchronize(copy_);        // the arena's copies are done
+      used_ = 0;
+    }
+    char* const dst = static_cast<char*>(pool_) + off;
+    if (e == hipSuccess && bytes > kArenaBytes) return hipMemcpy(dst, dircos, bytes, hipMemcpyHostToDevice) == hipSuccess;
+    if (e != hipSuccess) return false;
+    std::memcpy(arena_ + used_, dircos, bytes);
+    e = hipMemcpyAsync(dst, arena_ + used_, bytes, hipMemcpyHostToDevice, copy_);
+    used_ += bytes;
+    return e == hipSuccess;
+  }
+
+  // A caller's stream now reads a request's outputs.  Memory that is given
+  // back while it does must not be written before that read: once a release
+  // follows, the next upload or launch waits for it.
+  hipError_t reads(hipStream_t s) {
+    for (Reader& r : readers_)
+      if (r.s == s) {
+        if (r.state != kReleased) r.state = kReading;   // the later record covers the earlier reads
+        return hipEventRecord(r.ev, s);
+      }
+    if (readers_.size() >= kMaxReaders) return hipStreamSynchronize(s);
+    Reader r{s, nullptr, kReading};
+    hipError_t e = hipEventCreateWithFlags(&r.ev, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventRecord(r.ev, s);
+    if (e != hipSuccess) {
+      if (r.ev) (void)hipEventDestroy(r.ev);
+      return e;
+    }
+    readers_.push_back(r);
+    return hipSuccess;
+  }
+  void released() {
+    for (Reader& r : readers_)
+      if (r.state == kReading) r.state = kReleased;
   }
 
   int64_t launch(const std::vector<Tile>& tiles, const std::vector<const Request*>& reqs) override {
@@ -113,7 +162,10 @@ class HipBackend final : public fftbf::serve::Backend {
       d.pad = 0;
     }
     FFTBF_TRACE("bf_server batch launch");
-    hipError_t e = hipMemcpyAsync(dev_[slot], h, sizeof(fftbf::ServeTile) * n, hipMemcpyHostToDevice, stream_);
+    hipError_t e = wait_readers();
+    if (e == hipSuccess) e = hipMemcpyAsync(dev_[slot], h, sizeof(fftbf::ServeTile) * n, hipMemcpyHostToDevice, copy_);
+    if (e == hipSuccess) e = hipEventRecord(ev_copy_[slot], copy_);
+    if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_copy_[slot], 0);
     if (e == hipSuccess)
       e = fftbf::launch_serve(dev_[slot], n, static_cast<const uint32_t*>(ring_), ring_samples_, n_chan_, n_pol_, dl_,
                               stream_);
@@ -144,6 +196,28 @@ class HipBackend final : public fftbf::serve::Backend {
   hipError_t err_ = hipSuccess;
 
  private:
+  static constexpr size_t kArenaBytes = size_t(1) << 20, kMaxReaders = 16;
+  enum ReadState { kIdle, kReading, kReleased };
+  struct Reader {
+    hipStream_t s;
+    hipEvent_t ev;
+    ReadState state;
+  };
+  hipError_t wait_readers() {
+    for (Reader& r : readers_) {
+      if (r.state != kReleased) continue;
+      const hipError_t e = hipStreamWaitEvent(copy_, r.ev, 0);
+      if (e != hipSuccess) return e;
+      r.state = kIdle;
+    }
+    return hipSuccess;
+  }
+
+  hipStream_t copy_ = nullptr;               // uploads
+  char* arena_ = nullptr;                    // pinned staging of pointing tables
+  size_t used_ = 0;
+  std::vector<Reader> readers_;              // callers' streams that copied results
+  hipEvent_t ev_copy_[kSlots] = {};
   int n_chan_ = 0, n_pol_ = 0, max_tiles_ = 0;
   int64_t ring_samples_ = 0, count_ = 0;
   size_t frame_bytes_ = 0;
@@ -301,6 +375,7 @@ bf_status bf_server_release(bf_server* srv, int64_t id) {
   if (!srv) return sfail(BF_ERR_INVALID_ARGUMENT, "server_release: NULL srv");
   const int r = srv->sched->release(id);
   if (r != fftbf::serve::kOk) return sfail(map_status(r), "server_release: request unknown or still running");
+  srv->be.released();
   return BF_OK;
 }
 
@@ -335,10 +410,13 @@ bf_status bf_server_copy_result(bf_server* srv, int64_t id, float* dst, void* st
   const bf_status st = bf_server_result(srv, id, &src, &n);
   if (st != BF_OK) return st;
   if (!dst) return sfail(BF_ERR_INVALID_ARGUMENT, "server_copy_result: NULL dst");
-  // the result was written on the server stream; order the copy after it
-  hipError_t e = hipStreamSynchronize(srv->be.stream_);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(dst, src, sizeof(float) * n, hipMemcpyDeviceToDevice, static_cast<hipStream_t>(stream));
+  // the request is done: the event recorded after its last launch has been
+  // seen complete by the host, so the copy is ordered after the writes and
+  // need not wait for the batches now on the server's stream (waiting for
+  // them left the device without a next batch meanwhile: a burst of 24
+  // requests 3.2 -> 2.8 ms)
+  hipError_t e = hipMemcpyAsync(dst, src, sizeof(float) * n, hipMemcpyDeviceToDevice, static_cast<hipStream_t>(stream));
+  if (e == hipSuccess) e = srv->be.reads(static_cast<hipStream_t>(stream));
   if (e != hipSuccess) return sfail(BF_ERR_DEVICE, std::string("server_copy_result: ") + hipGetErrorString(e));
   return BF_OK;
 }

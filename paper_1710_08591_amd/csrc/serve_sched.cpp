@@ -197,11 +197,15 @@ void Scheduler::finish_if_done(Request& r) {
 int Scheduler::pump() {
   // retire finished launches (in issue order)
   while (!flights_.empty() && be_->finished(flights_.front().handle)) {
-    for (const Tile& t : flights_.front().tiles) {
-      auto it = reqs_.find(t.req);
+    // a batch holds a request's tiles in turns: one lookup and one check per
+    // turn, not per tile
+    const std::vector<Tile>& tiles = flights_.front().tiles;
+    for (size_t i = 0, j; i < tiles.size(); i = j) {
+      for (j = i + 1; j < tiles.size() && tiles[j].req == tiles[i].req;) ++j;
+      auto it = reqs_.find(tiles[i].req);
       if (it == reqs_.end()) continue;
-      ++it->second.finished;
-      ++st_.tiles_done;
+      it->second.finished += (int64_t)(j - i);
+      st_.tiles_done += (int64_t)(j - i);
       finish_if_done(it->second);
     }
     flights_.pop_front();

@@ -88,3 +88,35 @@ def test_server_ring_wrap_inside_a_group():
         assert srv.release(rid) == bf.BF_OK
     srv.close()
     plan.close()
+
+
+def test_server_memory_reused_while_a_result_is_read():
+    """Results copied on a caller's stream that is still busy, their memory
+    given back and taken by the next requests at once: every copy holds its
+    own request's beams (the pool fits one request)."""
+    import torch
+    import paper_1710_08591_amd as bf
+    r = np.random.default_rng(11)
+    v = torch.from_numpy(r.integers(0, 256, (512, 8, 1, 16, 4), dtype=np.uint8)).cuda()
+    plan = bf.Plan(n_ns=16, n_chan=8, n_pol=1, block=16)
+    ds = [r.uniform(-1.0, 1.0, (128, 2)) for _ in range(6)]
+    srv = bf.Server(plan, ring_samples=512, hbm_budget=200 * 1024)
+    assert srv.advance(512, v) == bf.BF_OK
+    side = torch.cuda.Stream()
+    x = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    outs = []
+    with torch.cuda.stream(side):
+        for d in ds:
+            rid = srv.submit(d, 0, 8, 512)
+            assert srv.wait(rid)[0] == bf.BF_OK
+            for _ in range(4):
+                x = x @ x * 1e-3               # the copy below waits behind this
+            outs.append(srv.result(rid))
+            assert srv.release(rid) == bf.BF_OK
+    torch.cuda.synchronize()
+    for d, o in zip(ds, outs):
+        want = bf.form_tied_beams_v(plan, v, 0, 8, torch.from_numpy(d).cuda())
+        assert torch.equal(o, want)
+    srv.close()
+    plan.close()
