@@ -193,9 +193,9 @@ bf_status bf_plan_create(const bf_plan_desc* desc, bf_plan** plan) {
     e = hipMalloc(&p->lag, fftbf::lag_table_bytes(d.n_ns));
     if (e == hipSuccess) e = fftbf::launch_lag_table(p->lag, d.n_ns, s);
   }
-  if (e == hipSuccess && d.precision != BF_PREC_FP32) {
-    e = hipMalloc(&p->mix, fftbf::mix_table_bytes(d.n_ns, d.precision));
-    if (e == hipSuccess) e = fftbf::launch_mix_tables(p->mix, d.n_ns, d.precision, s);
+  if (e == hipSuccess && fftbf::mix_window_supported(d.n_ns, d.precision)) {
+    e = hipMalloc(&p->mix, fftbf::mix_table_bytes(d.n_ns));
+    if (e == hipSuccess) e = fftbf::launch_mix_tables(p->mix, d.n_ns, s);
   }
   if (e == hipSuccess) e = ss.finish();
   if (e != hipSuccess) {
@@ -324,7 +324,7 @@ static bf_status beamform_fft_impl(const bf_plan* plan, const uint8_t* volts, in
     a.n_keep = keep_of(d);
     a.out = static_cast<float*>(out);
     a.norm = 1.0f / float(d.n_ew * d.n_ns);
-    e = fftbf::launch_mix(a, d.n_ns, d.precision, n_wg, s);
+    e = fftbf::launch_mix(a, d.n_ns, n_wg, s);
   }
   if (e != hipSuccess) return dev_fail(e, "beamform_fft: launch");
   return BF_OK;

@@ -486,11 +486,11 @@ __attribute__((amdgpu_waves_per_eu(fft32_min_waves<N, G, TAPER, CPLX, FOLD>())))
 // takes column k2 = 2 m + h of half h.  The pass-1 tangent values and the
 // pass-2 multipliers live in one LDS copy per workgroup (its four waves
 // share it), not in registers, and the next frame's voltages are loaded
-// during the second half only: about 125 registers and 10 KB of LDS per
-// wavefront, so four wavefronts fit per SIMD (two for the kernel above).
-// Intensities: k_fft32_h unwindowed and k_fft32_hw with a real window
-// (three wavefronts per SIMD); the complex-output variants of this lattice
-// take the kernel above.  Complex gains and an E-W axis zero-padded to 8
+// during the second half only; the window's LDS copy (4 KB) leaves room for
+// three workgroups of four wavefronts per CU, so the registers may take
+// three wavefronts per SIMD (two for the kernel above).  k_fft32_hw makes the
+// intensities with a real window; unwindowed intensities are k_lag's, and the
+// complex-output variants of this lattice take the kernel above.  Complex gains and an E-W axis zero-padded to 8
 // beams take the N-S-first kernels below (the N-S transform on the four E-W
 // antenna columns, then the E-W transform per N-S beam).
 constexpr int kHWpg = 4;                 // wavefronts per workgroup
@@ -519,11 +519,10 @@ struct HalfTw {
   }
 };
 
-// TAPER 1: real per-antenna weights h (Sec. "Controlling beam shape with
-// windowing"), applied to the decoded nibbles before the E-W DFT as in the
-// kernel above (WindowLane), from one LDS copy per workgroup.
-template <int TAPER = 0>
-__device__ __forceinline__ void fft32_h_run(const Fft32Args& p) {
+// Real per-antenna weights h (Sec. "Controlling beam shape with windowing"),
+// applied to the decoded nibbles before the E-W DFT as in the kernel above
+// (WindowLane), from one LDS copy per workgroup.
+__global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_hw(Fft32Args p) {
   constexpr int N = 256, G = 16, L = 16, M = 512;
   constexpr int NSL = dit_slots(G);
   constexpr int YS = L + 1;
@@ -535,9 +534,7 @@ __device__ __forceinline__ void fft32_h_run(const Fft32Args& p) {
   // put the 16 rows a lane group reads on different bank groups
   __shared__ __attribute__((aligned(16))) float lds_tab[2][G][kHRow];
   __shared__ cf lds_c16[G];                                           // whole twiddle of column k2 = 16
-  static_assert(TAPER == 0 || TAPER == 1, "unwindowed or a real window");
-  // the window [a_ns][a_ew] (TAPER 1)
-  __shared__ __attribute__((aligned(16))) float lds_h[TAPER == 1 ? N * 4 : 1];
+  __shared__ __attribute__((aligned(16))) float lds_h[N * 4];          // the window [a_ns][a_ew]
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -556,9 +553,7 @@ __device__ __forceinline__ void fft32_h_run(const Fft32Args& p) {
     const float2 w = p.tw[threadIdx.x * 32 + 16];
     lds_c16[threadIdx.x] = cf{w.x, w.y};
   }
-  if constexpr (TAPER == 1) {
-    for (int i = threadIdx.x; i < N * 4; i += 64 * kHWpg) lds_h[i] = p.taper[i];
-  }
+  for (int i = threadIdx.x; i < N * 4; i += 64 * kHWpg) lds_h[i] = p.taper[i];
   __syncthreads();
   const int64_t task = (int64_t)blockIdx.x * kHWpg + wave;
   if (task >= p.n_wg) return;
@@ -575,10 +570,7 @@ __device__ __forceinline__ void fft32_h_run(const Fft32Args& p) {
   cf* const row = &lds_y[lane * YS];
 
   {
-    int wre = 0, wim = 0;
-    WindowLane wl{};
-    if constexpr (TAPER != 0) wl = window_lane(e1);
-    else ew_weights(e1, wre, wim);
+    const WindowLane wl = window_lane(e1);
 
     float acc[2][G];
 #pragma unroll
@@ -595,21 +587,16 @@ __device__ __forceinline__ void fft32_h_run(const Fft32Args& p) {
       for (int j = 0; j < L; ++j) b[j] = __builtin_nontemporal_load(q + a1 + G * j);
       for (int it = 0; it < n_it; ++it) {
         cf x[L];
-        if constexpr (TAPER == 1) {
 #pragma unroll
-          for (int j = 0; j < L; ++j) {
-            const uint32_t d = b[j];
-            const float4 h = *reinterpret_cast<const float4*>(&lds_h[(a1 + G * j) * 4]);
-            const float h2 = wl.s * h.z, h3 = wl.s * h.w;
-            const float pr = fmaf(h2, nib(d, 20), h.x * nib(d, 4));
-            const float pim = fmaf(h2, nib(d, 16), h.x * nib(d, 0));
-            const float qr = fmaf(h3, nib(d, wl.ou + 16), h.y * nib(d, wl.ou));
-            const float qi = fmaf(h3, nib(d, wl.ov + 16), h.y * nib(d, wl.ov));
-            x[j] = cf{fmaf(wl.tr, qr, pr), fmaf(wl.ti, qi, pim)};
-          }
-        } else {
-#pragma unroll
-          for (int j = 0; j < L; ++j) x[j] = cf{(float)sdot8((int)b[j], wre), (float)sdot8((int)b[j], wim)};
+        for (int j = 0; j < L; ++j) {
+          const uint32_t d = b[j];
+          const float4 h = *reinterpret_cast<const float4*>(&lds_h[(a1 + G * j) * 4]);
+          const float h2 = wl.s * h.z, h3 = wl.s * h.w;
+          const float pr = fmaf(h2, nib(d, 20), h.x * nib(d, 4));
+          const float pim = fmaf(h2, nib(d, 16), h.x * nib(d, 0));
+          const float qr = fmaf(h3, nib(d, wl.ou + 16), h.y * nib(d, wl.ou));
+          const float qi = fmaf(h3, nib(d, wl.ov + 16), h.y * nib(d, wl.ov));
+          x[j] = cf{fmaf(wl.tr, qr, pr), fmaf(wl.ti, qi, pim)};
         }
         cf xo[L];
         padded_odd_t<L>(x, xo);
@@ -922,23 +909,12 @@ __global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3)))
   fft32_nsf_run<2, 4>(p);
 }
 
-__global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(4))) void k_fft32_h(Fft32Args p) {
-  fft32_h_run<0>(p);
-}
-
-// the window's LDS copy (4 KB) leaves room for three workgroups of four
-// wavefronts per CU, so the registers may take three wavefronts per SIMD
-__global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_hw(Fft32Args p) {
-  fft32_h_run<1>(p);
-}
-
-
 template <int N, int G, int T, int FOLD = 1>
 void launch_nt(const Fft32Args& a, bool cplx, hipStream_t s) {
   constexpr int W = fft32_wpg<N, G, T, FOLD>();
   const dim3 grid((unsigned)((a.n_wg + W - 1) / W)), threads(64 * W);
   if (cplx) hipLaunchKernelGGL((k_fft32<N, G, T, true, FOLD>), grid, threads, 0, s, a);
-  else hipLaunchKernelGGL((k_fft32<N, G, T, false, FOLD>), grid, threads, 0, s, a);
+  else if constexpr (N < 256) hipLaunchKernelGGL((k_fft32<N, G, T, false, FOLD>), grid, threads, 0, s, a);
 }
 
 // The one choice of the group size G for each transform length N (and fold):
@@ -970,14 +946,14 @@ template <int N>
 hipError_t launch_n(const Fft32Args& a, int taper, bool cplx, hipStream_t s) {
   constexpr int G = fft32_g(N, 1);
   if constexpr (N == 256) {
-    if (taper == 0 && !cplx) {       // the 4 x 256 intensities: half-size tiles, four waves per SIMD
+    if (!cplx) {                                   // the 4 x 256 intensities
       const dim3 grid((unsigned)((a.n_wg + kHWpg - 1) / kHWpg)), threads(64 * kHWpg);
-      if (a.ew_rows == 8) hipLaunchKernelGGL(k_fft32_ew8, grid, threads, 0, s, a);   // even and odd E-W beams
-      else hipLaunchKernelGGL(k_fft32_h, grid, threads, 0, s, a);
-      return hipGetLastError();
-    }
-    if ((taper == 1 || taper == 2) && !cplx) {   // windowed or gain-weighted 4 x 256 intensities
-      const dim3 grid((unsigned)((a.n_wg + kHWpg - 1) / kHWpg)), threads(64 * kHWpg);
+      if (taper == 0) {                            // unwindowed ones are k_lag's unless the E-W axis is padded
+        if (a.ew_rows != 8) return hipErrorNotSupported;
+        hipLaunchKernelGGL(k_fft32_ew8, grid, threads, 0, s, a);   // even and odd E-W beams
+        return hipGetLastError();
+      }
+      if (taper == 3) return hipErrorNotSupported;  // the odd beams come with the even ones
       if (a.ew_rows == 8) {                      // with the E-W axis padded: all eight E-W beams
         if (taper == 1) hipLaunchKernelGGL(k_fft32_ew8w, grid, threads, 0, s, a);
         else hipLaunchKernelGGL(k_fft32_ew8g, grid, threads, 0, s, a);

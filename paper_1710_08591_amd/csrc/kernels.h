@@ -148,28 +148,28 @@ struct LocArgs {
 };
 hipError_t launch_localize(const LocArgs& a, hipStream_t s);
 
-// mixed-precision (MFMA) beamformer
+// windowed intensities of FP16 plans (matrix cores)
 struct MixArgs {
   const uint32_t* volts;
   int64_t n_time;
   int n_chan, n_pol, n_pg, pol_iter, block;
-  const void* mat;         // per-precision DFT operand tables (plan-owned)
+  const void* mat;         // DFT operand tables (plan-owned)
   const float* taper;
   const int32_t* sel;
   int n_keep;
   float* out;
   float norm;
 };
-hipError_t launch_mix(const MixArgs& a, int n_ns, int prec, int64_t n_wg, hipStream_t s);
-size_t mix_table_bytes(int n_ns, int prec);
-hipError_t launch_mix_tables(void* mat, int n_ns, int prec, hipStream_t s);
+hipError_t launch_mix(const MixArgs& a, int n_ns, int64_t n_wg, hipStream_t s);
+size_t mix_table_bytes(int n_ns);
+hipError_t launch_mix_tables(void* mat, int n_ns, hipStream_t s);
+// the lattices and blocks that FP16 and FP8 plans take
 bool mix_supported(int n_ns, int prec, int block);
 // per-antenna real weights on the matrix cores (windowed data split into FP16 terms)
 bool mix_window_supported(int n_ns, int prec);
-// the 4 x 256 lattice (k_mix256.hip): stage 1 on the matrix cores (FP16 or
-// FP8), stage 2 in FP32
+// the 4 x 256 lattice (k_mix256.hip): stage 1 on the matrix cores, stage 2 in FP32
 size_t mix256_table_bytes();
-hipError_t launch_mix256_tables(void* mat, int prec, hipStream_t s);
-hipError_t launch_mix256(const MixArgs& a, int prec, int64_t n_wg, hipStream_t s);
+hipError_t launch_mix256_tables(void* mat, hipStream_t s);
+hipError_t launch_mix256(const MixArgs& a, int64_t n_wg, hipStream_t s);
 
 }  // namespace fftbf
