@@ -92,8 +92,11 @@ struct TiedArgs {
   int complex_out;
   void* out;
   int run_units;           // output units per workgroup run (set by the launcher)
+  int unit_split;          // wavefronts that share an output unit (set by the launcher)
 };
 hipError_t launch_tied(const TiedArgs& a, hipStream_t s);
+// from stored beams, m_ns = 64 ... 512, 16-byte aligned beams
+hipError_t launch_tied_stored(const TiedArgs& a, hipStream_t s);
 
 // one tile of the tied-beam server (4 x 16 lattice, 16-sample blocks)
 struct ServeTile {
