@@ -596,7 +596,7 @@ bf_status bf_form_tied_beams_v_noalloc(const bf_plan* plan, const uint8_t* volts
 
 struct bf_regrid {
   int n_chan = 0, n_pg = 0, m_ew = 0, m_ns = 0, n_ns = 0, n_target = 0, pad = 0, n_taps = 0;
-  float* w = nullptr;       // dense weights [n_chan][pad][m_ns]
+  uint32_t* w = nullptr;    // dense weights
   int* first = nullptr;     // compact kernels [n_chan][n_target]
   float* tw = nullptr;      //                 [n_chan][n_taps][n_target]
   float* wew = nullptr;     // 2-D pointings: E-W weights [n_chan][pad][8]
@@ -681,7 +681,7 @@ bf_status bf_regrid_create(const bf_plan* plan, const double* sin_theta, int32_t
     if (e == hipSuccess) e = hipMemcpyAsync(dcoef, coef.data(), sizeof(double) * d.n_ns, hipMemcpyHostToDevice, s);
   }
   if (n_taps == 0) {
-    if (e == hipSuccess) e = hipMalloc(&r->w, sizeof(float) * (size_t)r->n_chan * r->pad * r->m_ns);
+    if (e == hipSuccess) e = hipMalloc(&r->w, fftbf::regrid_weight_bytes(r->n_chan, r->n_target, r->m_ns));
     if (e == hipSuccess)
       e = fftbf::launch_regrid_weights(r->w, plan->dl, st, dcoef, r->n_chan, n_target, r->n_ns, r->m_ns, s);
   } else {
@@ -736,7 +736,7 @@ bf_status bf_regrid_create_2d(const bf_plan* plan, const double* dircos, int32_t
   if (e == hipSuccess) e = hipMallocAsync(reinterpret_cast<void**>(&dd), sizeof(double) * 2 * n_point, s);
   if (e == hipSuccess) e = hipMemcpyAsync(dd, dns.data(), sizeof(double) * n_point, hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemcpyAsync(dd + n_point, dew.data(), sizeof(double) * n_point, hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMalloc(&r->w, sizeof(float) * (size_t)r->n_chan * r->pad * r->m_ns);
+  if (e == hipSuccess) e = hipMalloc(&r->w, fftbf::regrid_weight_bytes(r->n_chan, r->n_target, r->m_ns));
   if (e == hipSuccess) e = hipMalloc(&r->wew, sizeof(float) * (size_t)r->n_chan * r->pad * 8);
   if (e == hipSuccess)
     e = fftbf::launch_regrid_weights(r->w, plan->dl, dd, nullptr, r->n_chan, n_point, r->n_ns, r->m_ns, s);

@@ -115,7 +115,7 @@ hipError_t launch_tied_lag(const TiedArgs& a, hipStream_t s);
 // intensity-domain regridding of FFT beams (N-S axis)
 struct RegridArgs {
   const float* in;         // [n_blk][n_chan][n_pg][m_ew][m_ns]
-  const float* w;          // [n_chan][n_target_pad][m_ns]
+  const uint32_t* w;       // dense weights (regrid_weight_bytes, launch_regrid_weights)
   float* out;              // [n_blk][n_chan][n_pg][m_ew][n_target]
   const int* first;        // compact kernels: [n_chan][n_target] first tap (mod m_ns)
   const float* tw;         //                  [n_chan][n_taps][n_target] tap weights
@@ -129,7 +129,8 @@ struct RegridArgs {
 constexpr int kRegridMaxTaps = 8;
 int regrid_target_pad(int n_target);
 // coef: device double [n] window lag coefficients, or nullptr for the pointed kernel
-hipError_t launch_regrid_weights(float* w, const double* dl, const double* sin_t, const double* coef, int n_chan,
+size_t regrid_weight_bytes(int n_chan, int n_target, int m);
+hipError_t launch_regrid_weights(uint32_t* w, const double* dl, const double* sin_t, const double* coef, int n_chan,
                                  int n_target, int n, int m, hipStream_t s);
 // E-W regridding weights of 2-D pointings, w[chan][target_pad][m_ew = 8]
 hipError_t launch_regrid_ew_weights(float* w, const double* dl, const double* dircos_ew, int n_chan, int n_target,
