@@ -299,11 +299,21 @@ hipError_t launch_mp(TiedArgs a, hipStream_t s) {
   a.unit_split = 1;
   while (a.unit_split < 4 && 8 * a.unit_split <= unit && n_unit * base * a.unit_split < 4096) a.unit_split *= 2;
   const int slots = kTsWaves / a.unit_split;
-  // as many runs as fill the chip, none shorter than a unit per slot
-  int64_t runs = (512 + base - 1) / base;
+  // The number of runs that ends soonest: rounds of resident workgroups times a
+  // run's turns of its wavefronts, and the weights that each workgroup makes
+  // first (about a third of a turn of whole units).
+  constexpr int kWgs = sizeof(TsLds<M, PT>) > 80 * 1024 ? 256 : 512;
   const int64_t max_runs = (n_unit + slots - 1) / slots;
-  if (runs > max_runs) runs = max_runs;
-  if (runs < 1) runs = 1;
+  int64_t runs = 1;
+  double best = 0.0;
+  for (int64_t r = 1; r <= max_runs && (r == 1 || base * (r - 1) < 4 * kWgs); ++r) {
+    const int64_t turns = ((n_unit + r - 1) / r + slots - 1) / slots;
+    const double cost = (double)((base * r + kWgs - 1) / kWgs) * ((double)turns + 0.3 * a.unit_split);
+    if (r == 1 || cost < best) {
+      best = cost;
+      runs = r;
+    }
+  }
   int64_t per = (n_unit + runs - 1) / runs;
   per = (per + slots - 1) / slots * slots;
   runs = (n_unit + per - 1) / per;
