@@ -14,16 +14,24 @@
 // starting beam.
 //
 // Each 64-lane wavefront owns 64 rows.  It takes their argmax four rows at
-// a time (lane l holds the PER consecutive beams from l PER on, the four
-// rows' loads in flight together, deterministic lowest-index tie break;
-// DPP rotations within rows of 16 lanes, then two lane permutes) and
-// leaves each row's K window beams in LDS; then every lane runs the Newton
-// phase for one row.  The window beams A_j = A_0 + j sit at u_j = u_0 - j/M,
-// so one sincospi pair of u_0 per evaluation gives every beam's sines and
-// cosines by the angle-addition formulas with the FP64 constants of j/M
-// (held in LDS); D and D' then follow in closed form (one division), with a
-// Taylor branch within 0.01 / (pi (2n-1)) of an integer, where the closed
-// form of D' cancels.
+// a time (lane l holds the PER consecutive beams from l PER on) while the next
+// four rows' loads are in flight: the largest value by a prefix maximum over
+// the lanes (DPP), its lowest index from the masks of the lanes that hold it
+// (one compare per beam of a lane, the rest on the scalar unit).  The four rows
+// pass through LDS, from where 16 lanes a row pick the K window beams; then
+// every lane runs the Newton phase for one row.  Bound by the reads: 131072
+// rows of 512 beams (268 MB) take 61 us, 4.4 TB/s; with each four rows' loads
+// waited for, a (value, index) argmax of about 120 vector instructions a row
+// and the closed form of D and D' beam by beam it took 79.
+//
+// The window beams A_j = A_0 + j sit at u_j = u_0 - j/M, and with M = 2 n,
+// N = 2 n - 1 = M - 1,
+//   D(u_j) = (-1)^j (P t_j - Q),  D'(u_j) = (-1)^j pi (M (Q t_j + P) - P (1 + t_j^2)),
+//   t_j = cot(pi u_j),  P = sin(pi M u_0),  Q = cos(pi M u_0),
+// so an evaluation is one sincospi pair of u_0 and one of M u_0, and per beam
+// the angle addition with the FP64 constants of j/M (held in LDS), one
+// reciprocal and the sums of (-1)^j b_j t_j and (-1)^j b_j t_j^2; a Taylor branch
+// within 0.01 / (pi N) of an integer takes over where these cancel.
 #include "dev_common.h"
 #include "kernels.h"
 
@@ -33,17 +41,28 @@ namespace {
 
 constexpr double kPiD = 3.14159265358979323846;
 
-// One step of the wavefront argmax: combine with the (value, index) that
-// the DPP control CTRL brings in (a rotation within each row of 16 lanes),
-// the larger value winning and the lower index on ties.
-template <int CTRL>
-__device__ __forceinline__ void argmax_dpp(float& best, int& bi) {
-  const float ov = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, best), CTRL, 0xF, 0xF, false));
-  const int oi = __builtin_amdgcn_update_dpp(0, bi, CTRL, 0xF, 0xF, false);
-  if (ov > best || (ov == best && oi < bi)) {
-    best = ov;
-    bi = oi;
-  }
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// max with the lane that the DPP control CTRL brings in, in the rows of ROWS
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float max_dpp(float v) {
+  const int x = __builtin_bit_cast(int, v);
+  return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(x, x, CTRL, ROWS, 0xF, false)));
+}
+
+// the largest of the wavefront's values, NaN ignored (NaN if there are only NaN)
+__device__ __forceinline__ float wave_max(float v) {
+  v = max_dpp<0x111, 0xF>(v);      // row_shr 1, 2, 4, 8: lane 15 of a row holds the row's
+  v = max_dpp<0x112, 0xF>(v);
+  v = max_dpp<0x114, 0xF>(v);
+  v = max_dpp<0x118, 0xF>(v);
+  v = max_dpp<0x142, 0xA>(v);      // row_bcast 15, 31: lane 63 holds all
+  v = max_dpp<0x143, 0xC>(v);
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
 // Window of up to KMAX beams per row (16 or 64); PER = max(1, m / 64) beams
@@ -53,14 +72,14 @@ template <int PER, bool VEC, int KMAX>
 __global__ __launch_bounds__(256) void k_localize(LocArgs a) {
   constexpr int WS = KMAX + 1;                     // padded LDS row of window beams
   __shared__ float win[4][64 * WS];
-  __shared__ double tab[4][KMAX];                  // cos, sin of pi j/M and of pi N j/M
+  __shared__ double tab[2][KMAX];                  // cos, sin of pi j/M
+  __shared__ __attribute__((aligned(16))) float rows[4][4][64 * PER];   // the four rows at hand
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = a.m, K = a.n_window, N = 2 * a.n - 1;
   const double inv_m = 1.0 / (double)m;
   if (threadIdx.x < KMAX) {
     const int jj = threadIdx.x;
     sincospi((double)jj * inv_m, &tab[1][jj], &tab[0][jj]);
-    sincospi((double)(N * jj) * inv_m, &tab[3][jj], &tab[2][jj]);
   }
   __syncthreads();
   const int64_t row0 = ((int64_t)blockIdx.x * 4 + wave) * 64;
@@ -70,8 +89,8 @@ __global__ __launch_bounds__(256) void k_localize(LocArgs a) {
 
   // ---- argmax of the wave's 64 rows, four at a time; window beams to LDS ----
   int my_a0 = 0;
-  for (int rb = 0; rb < 64; rb += 4) {
-    float v[4][PER];
+  float nv[4][PER];                                // the next four rows, in flight
+  auto load = [&](int rb) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int64_t rr = row0 + rb + r < a.n_rows ? row0 + rb + r : a.n_rows - 1;   // rows past the end: unused
@@ -80,61 +99,72 @@ __global__ __launch_bounds__(256) void k_localize(LocArgs a) {
 #pragma unroll
         for (int q = 0; q < PER / 4; ++q) {
           const float4 f = reinterpret_cast<const float4*>(x)[q];
-          v[r][4 * q] = f.x;
-          v[r][4 * q + 1] = f.y;
-          v[r][4 * q + 2] = f.z;
-          v[r][4 * q + 3] = f.w;
+          nv[r][4 * q] = f.x;
+          nv[r][4 * q + 1] = f.y;
+          nv[r][4 * q + 2] = f.z;
+          nv[r][4 * q + 3] = f.w;
         }
       } else {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-          v[r][i] = -INFINITY;
-          if (lane * PER + i < m) v[r][i] = x[i];   // lanes past a short row load nothing
+          nv[r][i] = -INFINITY;
+          if (lane * PER + i < m) nv[r][i] = x[i];   // lanes past a short row load nothing
         }
       }
     }
+  };
+  load(0);
+  for (int rb = 0; rb < 64; rb += 4) {
+    float v[4][PER];
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int i = 0; i < PER; ++i) v[r][i] = nv[r][i];
+    if (rb + 4 < 64) load(rb + 4);
+    int a0[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      float best = -INFINITY;
-      int bi = 0x7FFFFFFF;
+      float best = v[r][0];
+#pragma unroll
+      for (int i = 1; i < PER; ++i) best = fmaxf(best, v[r][i]);
+      best = wave_max(best);
+      // lowest lane that holds it, then that lane's lowest beam (no lane: 0)
+      uint64_t at[PER], any = 0;
 #pragma unroll
       for (int i = 0; i < PER; ++i) {
-        if (lane * PER + i < m && v[r][i] > best) {
-          best = v[r][i];
-          bi = lane * PER + i;
-        }
+        at[i] = __ballot(v[r][i] == best);
+        any |= at[i];
       }
-      // within each row of 16 lanes: rotations by 8, 4, 2, 1 (DPP row_ror)
-      argmax_dpp<0x128>(best, bi);
-      argmax_dpp<0x124>(best, bi);
-      argmax_dpp<0x122>(best, bi);
-      argmax_dpp<0x121>(best, bi);
-      // across the four rows
+      const int l = any ? __builtin_ctzll(any) : 0;
+      int i0 = 0;
 #pragma unroll
-      for (int off = 16; off < 64; off <<= 1) {
-        const float ov = __shfl_xor(best, off);
-        const int oi = __shfl_xor(bi, off);
-        if (ov > best || (ov == best && oi < bi)) {
-          best = ov;
-          bi = oi;
-        }
-      }
-      const int a0 = bi == 0x7FFFFFFF ? 0 : bi;
-      if (lane == rb + r) my_a0 = a0;
-      // window slot of each of this lane's beams: A = a0 - half + jj (mod m, a
-      // power of two), jj < K
+      for (int i = PER - 1; i >= 0; --i)
+        if (at[i] >> l & 1) i0 = i;
+      a0[r] = l * PER + i0;
+      if (lane == rb + r) my_a0 = a0[r];
+      float* const x = &rows[wave][r][lane * PER];
+      if constexpr (PER >= 4) {
 #pragma unroll
-      for (int i = 0; i < PER; ++i) {
-        const int A = lane * PER + i;
-        const int jj = (A - a0 + half) & (m - 1);
-        if (A < m && jj < K) w[(rb + r) * WS + jj] = v[r][i];
+        for (int q = 0; q < PER / 4; ++q)
+          reinterpret_cast<float4*>(x)[q] = make_float4(v[r][4 * q], v[r][4 * q + 1], v[r][4 * q + 2], v[r][4 * q + 3]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) x[i] = v[r][i];
       }
     }
+    wave_lds_sync();
+    // window beams A = a0 - half + jj (mod m, a power of two), jj < K
+    {
+      const int r = lane >> 4;
+      const int ar = r < 2 ? (r ? a0[1] : a0[0]) : (r == 2 ? a0[2] : a0[3]);
+#pragma unroll
+      for (int j0 = 0; j0 < KMAX; j0 += 16) {
+        const int jj = j0 + (lane & 15);
+        if (jj < K) w[(rb + r) * WS + jj] = rows[wave][r][(ar - half + jj) & (m - 1)];
+      }
+    }
+    wave_lds_sync();
   }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
   // ---- Newton phase: lane = row ----
   const int64_t row = row0 + lane;
   const bool row_ok = row < a.n_rows;
@@ -147,34 +177,32 @@ __global__ __launch_bounds__(256) void k_localize(LocArgs a) {
     // u_j = y - A_j / M with A_j = a0 - half + j; reduced to [-1/2, 1/2] for j = 0
     double u0 = y - (double)(my_a0 - half) * inv_m;
     u0 -= rint(u0);
-    double s0, c0, S0, C0;
+    double s0, c0, P, Q;
     sincospi(u0, &s0, &c0);
-    sincospi(Nd * u0, &S0, &C0);
-    double sp = 0.0, sdp = 0.0;
+    sincospi((double)m * u0, &P, &Q);
+    double sp = 0.0, sdp = 0.0;                      // of the beams at the singular point
+    double T0 = 0.0, T1 = 0.0, T2 = 0.0;             // sums of (-1)^j b_j t_j^k over the others
     for (int j = 0; j < K; ++j) {
-      const double bj = (double)wr[j];
-      const double u = u0 - (double)j * inv_m;
-      const double e = u - rint(u);
-      double d, dd;
-      if (fabs(Nd * e) < 0.01 / kPiD) {
-        const double x = kPiD * e, x2 = x * x, N2 = Nd * Nd;
+      const float b = wr[j];
+      const double cj = tab[0][j], sj = tab[1][j];
+      const double s = s0 * cj - c0 * sj, c = c0 * cj + s0 * sj;      // of pi u_j
+      if (fabs(Nd * s) < 0.01) {
+        const double x = copysign(s, s * c) * (1.0 + s * s / 6.0), x2 = x * x, N2 = Nd * Nd;
         const double c4 = (3.0 * N2 * N2 - 10.0 * N2 + 7.0);
-        d = Nd * (1.0 - (N2 - 1.0) * x2 / 6.0 + c4 * x2 * x2 / 360.0);
-        dd = kPiD * Nd * (-(N2 - 1.0) * x / 3.0 + c4 * x2 * x / 90.0);
+        sp = fma(Nd * (1.0 - (N2 - 1.0) * x2 / 6.0 + c4 * x2 * x2 / 360.0), (double)b, sp);
+        sdp = fma(kPiD * Nd * (-(N2 - 1.0) * x / 3.0 + c4 * x2 * x / 90.0), (double)b, sdp);
       } else {
-        // sin, cos of pi u and of N pi u by angle addition (u = u0 - j/M)
-        const double cj = tab[0][j], sj = tab[1][j], Cj = tab[2][j], Sj = tab[3][j];
-        const double s = s0 * cj - c0 * sj, c = c0 * cj + s0 * sj;
-        const double S = S0 * Cj - C0 * Sj, C = C0 * Cj + S0 * Sj;
-        const double inv = 1.0 / s;                 // one division: dD = pi (N C - D c) / s
-        d = S * inv;
-        dd = kPiD * (Nd * C - d * c) * inv;
+        double r = __builtin_amdgcn_rcp(s);
+        r = fma(fma(-s, r, 1.0), r, r);
+        r = fma(fma(-s, r, 1.0), r, r);
+        const double t = c * r, bj = (double)(j & 1 ? -b : b), bt = bj * t;
+        T0 += bj;
+        T1 += bt;
+        T2 = fma(bt, t, T2);
       }
-      sp = fma(d, bj, sp);
-      sdp = fma(dd, bj, sdp);
     }
-    p = sp * inv_m;
-    dp = sdp * inv_m;
+    p = (sp + (P * T1 - Q * T0)) * inv_m;
+    dp = (sdp + kPiD * ((double)m * (Q * T1 + P * T0) - P * (T0 + T2))) * inv_m;
   };
 
   double y = y0, p, dp;
@@ -229,7 +257,7 @@ hipError_t launch_loc_k(const LocArgs& a, unsigned nb, hipStream_t s) {
 
 hipError_t launch_localize(const LocArgs& a, hipStream_t s) {
   if (a.n_rows <= 0) return hipSuccess;
-  if (a.n_window < 1 || a.n_window > 64 || a.n_window > a.m) return hipErrorInvalidValue;
+  if (a.m != 2 * a.n || a.n_window < 1 || a.n_window > 64 || a.n_window > a.m) return hipErrorInvalidValue;
   const int64_t nb = (a.n_rows + 255) / 256;      // 64 rows per wavefront, 4 wavefronts per workgroup
   if (nb > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   return a.n_window <= 16 ? launch_loc_k<16>(a, (unsigned)nb, s) : launch_loc_k<64>(a, (unsigned)nb, s);
