@@ -193,7 +193,9 @@ bf_status bf_plan_create(const bf_plan_desc* desc, bf_plan** plan) {
     e = hipMalloc(&p->lag, fftbf::lag_table_bytes(d.n_ns));
     if (e == hipSuccess) e = fftbf::launch_lag_table(p->lag, d.n_ns, s);
   }
-  if (e == hipSuccess && fftbf::mix_window_supported(d.n_ns, d.precision)) {
+  // operand tables of the weighted intensities on the matrix cores: FP16 plans, 4 x 256 FP32 plans
+  if (e == hipSuccess && d.m_ew == 4 && !folded &&
+      (d.precision == BF_PREC_FP32 ? d.n_ns == 256 : fftbf::mix_window_supported(d.n_ns, d.precision))) {
     e = hipMalloc(&p->mix, fftbf::mix_table_bytes(d.n_ns));
     if (e == hipSuccess) e = fftbf::launch_mix_tables(p->mix, d.n_ns, s);
   }
@@ -274,7 +276,7 @@ static bf_status beamform_fft_impl(const bf_plan* plan, const uint8_t* volts, in
     a.out = static_cast<float*>(out);
     a.norm = 1.0f / float(d.n_ew * d.n_ns);
     e = fftbf::launch_lag(a, d.n_ns, s);
-  } else if (d.precision == BF_PREC_FP32) {
+  } else if (d.precision == BF_PREC_FP32 && !(kind == BF_OUT_INTENSITY && taper && plan->mix)) {
     fftbf::Fft32Args a{};
     a.volts = reinterpret_cast<const uint32_t*>(volts);
     a.n_time = n_time;
@@ -319,12 +321,15 @@ static bf_status beamform_fft_impl(const bf_plan* plan, const uint8_t* volts, in
     a.pol_iter = (n_pg == 1) ? d.n_pol : 1;
     a.block = d.block;
     a.mat = plan->mix;
+    a.tw = plan->tw;
+    a.mult = plan->mult;
     a.taper = taper;
     a.sel = plan->sel;
     a.n_keep = keep_of(d);
     a.out = static_cast<float*>(out);
     a.norm = 1.0f / float(d.n_ew * d.n_ns);
-    e = fftbf::launch_mix(a, d.n_ns, n_wg, s);
+    a.gains = taper_kind == 2;
+    e = d.precision == BF_PREC_FP32 ? fftbf::launch_mix256(a, true, n_wg, s) : fftbf::launch_mix(a, d.n_ns, n_wg, s);
   }
   if (e != hipSuccess) return dev_fail(e, "beamform_fft: launch");
   return BF_OK;

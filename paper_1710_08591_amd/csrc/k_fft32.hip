@@ -486,13 +486,11 @@ __attribute__((amdgpu_waves_per_eu(fft32_min_waves<N, G, TAPER, CPLX, FOLD>())))
 // takes column k2 = 2 m + h of half h.  The pass-1 tangent values and the
 // pass-2 multipliers live in one LDS copy per workgroup (its four waves
 // share it), not in registers, and the next frame's voltages are loaded
-// during the second half only; the window's LDS copy (4 KB) leaves room for
-// three workgroups of four wavefronts per CU, so the registers may take
-// three wavefronts per SIMD (two for the kernel above).  k_fft32_hw makes the
-// intensities with a real window; unwindowed intensities are k_lag's, and the
-// complex-output variants of this lattice take the kernel above.  Complex gains and an E-W axis zero-padded to 8
-// beams take the N-S-first kernels below (the N-S transform on the four E-W
-// antenna columns, then the E-W transform per N-S beam).
+// during the second half only, so three wavefronts fit per SIMD (two for the
+// kernel above).  The intensities with the E-W axis zero-padded to 8 beams
+// take it, N-S first: the N-S transform on the four E-W antenna columns, then
+// the E-W transform per N-S beam.  The complex-output variants of this lattice
+// take the kernel above.
 constexpr int kHWpg = 4;                 // wavefronts per workgroup
 constexpr int kHRow = 44;                // LDS floats per (half, a1) row: 16 tangents, 25 multipliers, pad
 
@@ -518,170 +516,6 @@ struct HalfTw {
     if constexpr (MI + 1 < 16) HalfTw<H, MI + 1>::run(y, t1, c16, row);
   }
 };
-
-// Real per-antenna weights h (Sec. "Controlling beam shape with windowing"),
-// applied to the decoded nibbles before the E-W DFT as in the kernel above
-// (WindowLane), from one LDS copy per workgroup.
-__global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_hw(Fft32Args p) {
-  constexpr int N = 256, G = 16, L = 16, M = 512;
-  constexpr int NSL = dit_slots(G);
-  constexpr int YS = L + 1;
-  static_assert(L + NSL <= kHRow && kHRow % 4 == 0 && (kHRow / 4) % 2 == 1, "table rows");
-  static_assert((4 * M + 34) * 4 <= 64 * YS * 8, "block-end sums must fit the tile");
-  __shared__ cf lds_tiles[kHWpg * 64 * YS];
-  // [h][a1][44]: floats 0-15 the tangents of W_512^{a1 (2m + h)}, 16-40
-  // the pass-2 multipliers of column k2 = 2 a1 + h; rows of 11 float4 chunks
-  // put the 16 rows a lane group reads on different bank groups
-  __shared__ __attribute__((aligned(16))) float lds_tab[2][G][kHRow];
-  __shared__ cf lds_c16[G];                                           // whole twiddle of column k2 = 16
-  __shared__ __attribute__((aligned(16))) float lds_h[N * 4];          // the window [a_ns][a_ew]
-
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  cf* const lds_y = lds_tiles + wave * 64 * YS;
-  const int e1 = lane >> 4, a1 = lane & 15;
-
-  for (int i = threadIdx.x; i < 2 * G * L; i += 64 * kHWpg) {
-    const int h = i / (G * L), r = i % (G * L), aa = r / L, m = r % L;
-    lds_tab[h][aa][m] = p.tw[aa * 32 + 2 * m + h].x;
-  }
-  for (int i = threadIdx.x; i < 32 * NSL; i += 64 * kHWpg) {
-    const int k2 = i / NSL;
-    lds_tab[k2 & 1][k2 >> 1][L + i % NSL] = p.mult[i];
-  }
-  if (threadIdx.x < G) {
-    const float2 w = p.tw[threadIdx.x * 32 + 16];
-    lds_c16[threadIdx.x] = cf{w.x, w.y};
-  }
-  for (int i = threadIdx.x; i < N * 4; i += 64 * kHWpg) lds_h[i] = p.taper[i];
-  __syncthreads();
-  const int64_t task = (int64_t)blockIdx.x * kHWpg + wave;
-  if (task >= p.n_wg) return;
-  int wg = (int)task;
-  const int pg = wg % p.n_pg;
-  wg /= p.n_pg;
-  const int chan = wg % p.n_chan;
-  const int blk = wg / p.n_chan;
-
-  const int64_t t_base = (int64_t)blk * p.block;
-  const int n_it = p.block;
-  const int64_t frame_stride = (int64_t)(p.chan_stride ? p.chan_stride : p.n_chan) * p.n_pol * N;
-  const int n_valid = (int)((p.n_time - t_base) < p.block ? (p.n_time - t_base) : p.block);
-  cf* const row = &lds_y[lane * YS];
-
-  {
-    const WindowLane wl = window_lane(e1);
-
-    float acc[2][G];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int k = 0; k < G; ++k) acc[h][k] = 0.f;
-
-    for (int pi = 0; pi < p.pol_iter; ++pi) {
-      const int pol = (p.pol_iter == 1) ? pg : pi;
-      // the frame pointer is the wavefront's (scalar); the lane adds a1
-      const uint32_t* q = p.volts + ((int64_t)chan * p.n_pol + pol) * N + t_base * frame_stride;
-      uint32_t b[L];
-#pragma unroll
-      for (int j = 0; j < L; ++j) b[j] = __builtin_nontemporal_load(q + a1 + G * j);
-      for (int it = 0; it < n_it; ++it) {
-        cf x[L];
-#pragma unroll
-        for (int j = 0; j < L; ++j) {
-          const uint32_t d = b[j];
-          const float4 h = *reinterpret_cast<const float4*>(&lds_h[(a1 + G * j) * 4]);
-          const float h2 = wl.s * h.z, h3 = wl.s * h.w;
-          const float pr = fmaf(h2, nib(d, 20), h.x * nib(d, 4));
-          const float pim = fmaf(h2, nib(d, 16), h.x * nib(d, 0));
-          const float qr = fmaf(h3, nib(d, wl.ou + 16), h.y * nib(d, wl.ou));
-          const float qi = fmaf(h3, nib(d, wl.ov + 16), h.y * nib(d, wl.ov));
-          x[j] = cf{fmaf(wl.tr, qr, pr), fmaf(wl.ti, qi, pim)};
-        }
-        cf xo[L];
-        padded_odd_t<L>(x, xo);
-        dit<L>(x);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const cf* y = h ? xo : x;
-          if (h == 1) {
-            // the next frame's loads, in flight through this half (past the
-            // block: the buffer's first frame, cached)
-            q = (it + 1 >= n_it) ? p.volts : ((it + 1 < n_valid) ? q + frame_stride : q);
-#pragma unroll
-            for (int j = 0; j < L; ++j) b[j] = __builtin_nontemporal_load(q + a1 + G * j);
-          }
-          {
-            float t1[L];
-            const float4* tp = reinterpret_cast<const float4*>(&lds_tab[h][a1][0]);
-#pragma unroll
-            for (int k = 0; k < L / 4; ++k) {
-              const float4 v = tp[k];
-              t1[4 * k] = v.x;
-              t1[4 * k + 1] = v.y;
-              t1[4 * k + 2] = v.z;
-              t1[4 * k + 3] = v.w;
-            }
-            // (the whole twiddle of column 16 is read per frame: held across
-            // the frame loop it would take the last free register)
-            if (h == 0) HalfTw<0, 0>::run(y, t1, lds_c16[a1], row);
-            else HalfTw<1, 0>::run(y, t1, cf{}, row);
-          }
-          wave_lds_sync();
-          cf z[G];
-#pragma unroll
-          for (int j = 0; j < G; ++j) z[j] = lds_y[(e1 * 16 + j) * YS + a1];
-          wave_lds_sync();
-          float mu[28];
-          const float4* mp = reinterpret_cast<const float4*>(&lds_tab[h][a1][L]);
-#pragma unroll
-          for (int k = 0; k < 7; ++k) {
-            const float4 v = mp[k];
-            mu[4 * k] = v.x;
-            mu[4 * k + 1] = v.y;
-            mu[4 * k + 2] = v.z;
-            mu[4 * k + 3] = v.w;
-          }
-          dit_rs<G>(z, mu);
-#pragma unroll
-          for (int k1 = 0; k1 < G; ++k1) acc[h][k1] = cnorm_acc(z[k1], acc[h][k1]);
-        }
-      }
-    }
-
-    // ---- block end: the kept beams of the channel, coalesced stores ----
-    // E-W beam e's sums start at 512 e + (e & 1) + 32 (e >> 1): the four lane
-    // groups of one store then cover all 64 banks
-    float* lds_i = reinterpret_cast<float*>(lds_y);
-    auto ebase = [](int e) { return e * M + (e & 1) + 32 * (e >> 1); };
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int k1 = 0; k1 < G; ++k1) lds_i[ebase(e1) + 2 * a1 + h + 32 * k1] = acc[h][k1];
-    wave_lds_sync();
-    const int keep = p.n_keep;
-    const int32_t* sel = p.sel ? p.sel + (int64_t)chan * keep : nullptr;
-    float* o = static_cast<float*>(p.out) + (((int64_t)blk * p.n_chan + chan) * p.n_pg + pg) * p.ew_rows * keep;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int r = e * p.ew_mul + p.ew_off;
-      for (int j = lane; j < keep; j += 64) {
-        const int A = sel ? sel[j] : j;
-        o[r * keep + j] = lds_i[ebase(e) + A] * p.norm;
-      }
-    }
-  }
-}
-
-// |B|^2 of the four beams of the unpadded 4-point E-W transform of one N-S
-// beam, from its four E-W antenna columns z_q, added to acc[e]
-__device__ __forceinline__ void ew4_beams_acc(const cf* z, float* acc) {
-  const cf s02 = cadd(z[0], z[2]), d02 = csub(z[0], z[2]), s13 = cadd(z[1], z[3]), d13 = csub(z[1], z[3]);
-  acc[0] = cnorm_acc(cadd(s02, s13), acc[0]);
-  acc[2] = cnorm_acc(csub(s02, s13), acc[2]);
-  acc[1] = cnorm_acc(cf{d02.r + d13.i, d02.i - d13.r}, acc[1]);   // d02 - i d13
-  acc[3] = cnorm_acc(cf{d02.r - d13.i, d02.i + d13.r}, acc[3]);   // d02 + i d13
-}
 
 // |B|^2 of the eight beams of the zero-padded 8-point E-W transform of one
 // N-S beam, from its four E-W antenna columns z_q, added to acc[E]: the even
@@ -719,9 +553,8 @@ __device__ __forceinline__ void ew8_beams_acc(const cf* z, float* acc) {
 // that each round fits the tile.  TAPER 1 (real per-antenna weights) and 2
 // (complex gains, or real weights when gain_src is 1) scale each decoded
 // antenna value before the N-S transform, from one LDS copy per workgroup.
-template <int TAPER, int MEW>
+template <int TAPER>
 __device__ __forceinline__ void fft32_nsf_run(const Fft32Args& p) {
-  static_assert(MEW == 4 || MEW == 8, "E-W transform of 4 or 8 beams");
   constexpr int N = 256, G = 16, L = 16, M = 512;
   constexpr int NSL = dit_slots(G);
   constexpr int YS = L + 1;
@@ -776,13 +609,13 @@ __device__ __forceinline__ void fft32_nsf_run(const Fft32Args& p) {
   cf* const row = &lds_y[lane * YS];
   const int sh_re = 8 * e1 + 4, sh_im = 8 * e1;    // antenna e1: real part high nibble, imaginary low
 
-  float acc[2][4][MEW];
+  float acc[2][4][8];
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int e = 0; e < MEW; ++e) acc[h][r][e] = 0.f;
+      for (int e = 0; e < 8; ++e) acc[h][r][e] = 0.f;
 
   for (int pi = 0; pi < p.pol_iter; ++pi) {
     const int pol = (p.pol_iter == 1) ? pg : pi;
@@ -858,8 +691,7 @@ __device__ __forceinline__ void fft32_nsf_run(const Fft32Args& p) {
           cf zq[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) zq[c] = lds_y[(4 * e1 + r) * 64 + c * 16 + a1];
-          if constexpr (MEW == 8) ew8_beams_acc(zq, acc[h][r]);
-          else ew4_beams_acc(zq, acc[h][r]);
+          ew8_beams_acc(zq, acc[h][r]);
         }
         wave_lds_sync();
       }
@@ -873,20 +705,20 @@ __device__ __forceinline__ void fft32_nsf_run(const Fft32Args& p) {
   const int32_t* sel = p.sel ? p.sel + (int64_t)chan * keep : nullptr;
   float* o = static_cast<float*>(p.out) + (((int64_t)blk * p.n_chan + chan) * p.n_pg + pg) * p.ew_rows * keep;
 #pragma unroll
-  for (int odd = 0; odd < MEW / 4; ++odd) {
+  for (int odd = 0; odd < 2; ++odd) {
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          lds_i[ebase(e) + 2 * a1 + h + 32 * (4 * e1 + r)] = acc[h][r][MEW == 8 ? 2 * e + odd : e];
+          lds_i[ebase(e) + 2 * a1 + h + 32 * (4 * e1 + r)] = acc[h][r][2 * e + odd];
     wave_lds_sync();
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       for (int j = lane; j < keep; j += 64) {
         const int A = sel ? sel[j] : j;
-        o[(MEW == 8 ? 2 * e + odd : e * p.ew_mul + p.ew_off) * keep + j] = lds_i[ebase(e) + A] * p.norm;
+        o[(2 * e + odd) * keep + j] = lds_i[ebase(e) + A] * p.norm;
       }
     }
     wave_lds_sync();
@@ -894,19 +726,15 @@ __device__ __forceinline__ void fft32_nsf_run(const Fft32Args& p) {
 }
 
 __global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_ew8(Fft32Args p) {
-  fft32_nsf_run<0, 8>(p);
+  fft32_nsf_run<0>(p);
 }
 
 __global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_ew8w(Fft32Args p) {
-  fft32_nsf_run<1, 8>(p);
+  fft32_nsf_run<1>(p);
 }
 
 __global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_ew8g(Fft32Args p) {
-  fft32_nsf_run<2, 8>(p);
-}
-
-__global__ __launch_bounds__(64 * kHWpg) __attribute__((amdgpu_waves_per_eu(3))) void k_fft32_ng(Fft32Args p) {
-  fft32_nsf_run<2, 4>(p);
+  fft32_nsf_run<2>(p);
 }
 
 template <int N, int G, int T, int FOLD = 1>
@@ -946,22 +774,14 @@ template <int N>
 hipError_t launch_n(const Fft32Args& a, int taper, bool cplx, hipStream_t s) {
   constexpr int G = fft32_g(N, 1);
   if constexpr (N == 256) {
-    if (!cplx) {                                   // the 4 x 256 intensities
+    // 4 x 256 intensities: here with the E-W axis padded, even and odd E-W
+    // beams at once; else unwindowed ones are k_lag's, weighted ones k_mix256's
+    if (!cplx) {
+      if (a.ew_rows != 8 || taper < 0 || taper > 2) return hipErrorNotSupported;
       const dim3 grid((unsigned)((a.n_wg + kHWpg - 1) / kHWpg)), threads(64 * kHWpg);
-      if (taper == 0) {                            // unwindowed ones are k_lag's unless the E-W axis is padded
-        if (a.ew_rows != 8) return hipErrorNotSupported;
-        hipLaunchKernelGGL(k_fft32_ew8, grid, threads, 0, s, a);   // even and odd E-W beams
-        return hipGetLastError();
-      }
-      if (taper == 3) return hipErrorNotSupported;  // the odd beams come with the even ones
-      if (a.ew_rows == 8) {                      // with the E-W axis padded: all eight E-W beams
-        if (taper == 1) hipLaunchKernelGGL(k_fft32_ew8w, grid, threads, 0, s, a);
-        else hipLaunchKernelGGL(k_fft32_ew8g, grid, threads, 0, s, a);
-      } else if (taper == 1) {
-        hipLaunchKernelGGL(k_fft32_hw, grid, threads, 0, s, a);
-      } else {
-        hipLaunchKernelGGL(k_fft32_ng, grid, threads, 0, s, a);
-      }
+      if (taper == 0) hipLaunchKernelGGL(k_fft32_ew8, grid, threads, 0, s, a);
+      else if (taper == 1) hipLaunchKernelGGL(k_fft32_ew8w, grid, threads, 0, s, a);
+      else hipLaunchKernelGGL(k_fft32_ew8g, grid, threads, 0, s, a);
       return hipGetLastError();
     }
   }

@@ -448,7 +448,7 @@ hipError_t launch_mix_tables(void* mat, int n_ns, hipStream_t s) {
 
 hipError_t launch_mix(const MixArgs& a, int n_ns, int64_t n_wg_blocks, hipStream_t s) {
   if (!a.taper || !mix_supported(n_ns, kPrecFp16, a.block)) return hipErrorNotSupported;
-  if (n_ns == 256) return launch_mix256(a, n_wg_blocks, s);
+  if (n_ns == 256) return launch_mix256(a, false, n_wg_blocks, s);
   const int64_t n_blk = a.n_time / a.block;
   const int64_t n_run = (n_blk + kMixBlocksPerWave - 1) / kMixBlocksPerWave;
   const int64_t n_wg = n_run * a.n_chan * a.n_pg;

@@ -1,5 +1,6 @@
-// Windowed FP16 FFT beamformer on the matrix cores for the 4 x 256 lattice
-// (gfx950): intensities of FP16 plans with real per-antenna weights.
+// Weighted FFT-beam intensities of the 4 x 256 lattice (gfx950): real
+// per-antenna windows (Sec. "Controlling beam shape with windowing") and
+// complex gains.
 //
 // The N-S transform is zero-padded to M = 512 (eq. e:fftbeamform, weights
 // of eq. e:w_A^a) and split as 512 = 32 x 16:
@@ -10,24 +11,30 @@
 //
 // Stage 1 is a dense product on the matrix cores, per sample and E-W beam:
 //   C[a1][k2] = A[a1][(a2, re|im)] * B[(a2, re|im)][k2]
-// A holds the windowed E-W sums of the E-W beam at N-S position a1 + 16 a2 and
+// A holds the weighted E-W sums of the E-W beam at N-S position a1 + 16 a2 and
 // B the realified coefficients, each as two FP16 terms (hi + lo, about 22
-// significant bits); three products accumulate into the same FP32
-// accumulators, so stage 1 is accurate to FP32 rounding.
+// significant bits); three products, the smallest first, accumulate into the
+// same FP32 accumulators, so stage 1 is accurate to FP32 rounding.
 //
-// The twiddle is a whole complex product in FP32 (four operations per
-// value).  Its tangent form (two operations, the factor Re W carried into
-// per-column stage-2 multipliers, as in the FP32 kernel) issues fewer vector
-// instructions, but the 25 multipliers per lane took the kernel past the 168
-// registers of three wavefronts per SIMD, and it measured no faster.
-//
-// Stage 2 is the FP32 16-point DFT over a1 in registers (compile-time
-// coefficients), one (E-W beam, k2) per lane.  The data go from the stage-1 layout (lane = (a1 group, k2)) to
+// Stage 2 is the FP32 16-point DFT over a1 in registers, one (E-W beam, k2)
+// per lane.  The data go from the stage-1 layout (lane = (a1 group, k2)) to
 // the stage-2 layout (lane = (E-W beam, k2), all a1) through an LDS tile of
 // one E-W beam pair at a time (9 KB per wavefront), so three wavefronts per
 // SIMD fit.  |B|^2 accumulates in registers over the block; at its end the
 // sums pass once more through LDS so the kept beams of the channel's clamp
 // table can be stored with coalesced writes.
+//
+// FP32 plans (TAN): the twiddle in tangent form, one fused multiply-add per
+// component, the factor Re W carried into stage 2 as the 25 multipliers of
+// column k2 (LDS, two wavefronts share them and the weights).  FP16 plans:
+// whole twiddles, the weights in registers; faster, less accurate.
+// 4 x 256, 64 channels, 2 polarisations, 256 blocks of 16 samples, 2-norm
+// errors against 64 bits: FP32 window 1065 -> 860 us (1.05e-7 -> 1.02e-7; the
+// whole transform on the vector units before), FP16 window 832 -> 790 us
+// (1.14e-7 -> 1.10e-7).  Bound by vector issue: about 750 instructions per
+// frame and wavefront, 48 matrix products behind them (a fourth product each
+// costs nothing).  Both stages on the matrix cores, without the LDS tile, took
+// 893 us: splitting Z costs what the DFT's instructions do.
 #include "dev_common.h"
 #include "dev_f16.h"
 #include "kernels.h"
@@ -40,7 +47,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // plan table layout (bytes)
 constexpr size_t kH256B1Off = 0;      // [term 2][kt 2][part 2][lane 64][8] halves
-constexpr size_t kH256TwOff = 8192;   // [lane 64][kt 2][q 4] float2
+constexpr size_t kH256TwOff = 8192;   // FP16 plans: [lane 64][kt 2][q 4] float2
 constexpr size_t kH256Bytes = 8192 + 4096;
 
 // realified coefficient of stage 1: output part `part` (0 Re, 1 Im) of k2
@@ -82,44 +89,88 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Windowed E-W sums (per-antenna real weights h, Sec. "Controlling beam shape
-// with windowing") of the lane's four N-S positions for all four E-W beams:
-// x[e][2 i], x[e][2 i + 1] = Re, Im of sum_q h_q z_q (-i)^{e q} at position i.
-__device__ __forceinline__ void ew_windowed(const uint32_t* dw, const float (&h)[4][4], float (&x)[4][8]) {
+// Weighted E-W sums of one N-S position (dword d: byte q holds antenna q, real
+// part in its high nibble) for all four E-W beams, sum_q h_q z_q (-i)^{e q}
+// with h real (4 floats) or complex (GAIN: 8).
+template <bool GAIN>
+__device__ __forceinline__ void ew_weighted(uint32_t d, const float* h, cf (&b)[4]) {
+  cf z[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    cf w[4];
+  for (int q = 0; q < 4; ++q)
+    z[q] = cf{(float)(int)__builtin_amdgcn_sbfe((int)d, 8 * q + 4, 4), (float)(int)__builtin_amdgcn_sbfe((int)d, 8 * q, 4)};
+  cf s[2], m[2];                             // x_0 + x_2, x_1 + x_3 and the differences
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-      w[q] = cf{h[i][q] * (float)(int)__builtin_amdgcn_sbfe((int)dw[i], 8 * q + 4, 4),
-                h[i][q] * (float)(int)__builtin_amdgcn_sbfe((int)dw[i], 8 * q, 4)};
-    const cf s02 = cadd(w[0], w[2]), d02 = csub(w[0], w[2]), s13 = cadd(w[1], w[3]), d13 = csub(w[1], w[3]);
-    const cf b[4] = {cadd(s02, s13), cf{d02.r + d13.i, d02.i - d13.r}, csub(s02, s13), cf{d02.r - d13.i, d02.i + d13.r}};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      x[e][2 * i] = b[e].r;
-      x[e][2 * i + 1] = b[e].i;
+  for (int k = 0; k < 2; ++k) {
+    const cf u = z[k], v = z[k + 2];
+    if constexpr (GAIN) {
+      const cf hu{h[2 * k], h[2 * k + 1]}, hv{h[2 * k + 4], h[2 * k + 5]};
+      const cf w = cmul(u, hu);
+      s[k] = cf{fmaf(-hv.i, v.i, fmaf(hv.r, v.r, w.r)), fmaf(hv.i, v.r, fmaf(hv.r, v.i, w.i))};
+      m[k] = cf{fmaf(hv.i, v.i, fmaf(-hv.r, v.r, w.r)), fmaf(-hv.i, v.r, fmaf(-hv.r, v.i, w.i))};
+    } else {
+      const cf w{h[k] * u.r, h[k] * u.i};
+      s[k] = cf{fmaf(h[k + 2], v.r, w.r), fmaf(h[k + 2], v.i, w.i)};
+      m[k] = cf{fmaf(-h[k + 2], v.r, w.r), fmaf(-h[k + 2], v.i, w.i)};
     }
   }
+  b[0] = cadd(s[0], s[1]);
+  b[1] = cf{m[0].r + m[1].i, m[0].i - m[1].r};
+  b[2] = csub(s[0], s[1]);
+  b[3] = cf{m[0].r - m[1].i, m[0].i + m[1].r};
 }
 
 // One wavefront per (block, channel, polarisation group).  Lane l = 16 g + n:
 // stage 1 holds a1 = 4 g + q (q < 4) and k2 = 16 kt + n (kt < 2); stage 2
-// takes E-W beam 2 p + (l >> 5) of pair p and k2 = l & 31.
-// The windowed E-W sums are split into FP16 hi + lo and stage 1 takes three
-// products (hi x hi, hi x lo, lo x hi of data and coefficients).  The
-// window is scaled by a power of two per wavefront so that its largest
-// weight lies in [1/2, 1) and the low terms stay in FP16's normal range;
-// the block sums are scaled back exactly.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_mix256(MixArgs a) {
-  constexpr int N = 256, M = 512;
+// takes E-W beam 2 p + (l >> 5) of pair p and k2 = l & 31.  The weights are
+// scaled by a power of two so that the largest lies in [1/2, 1) and the low
+// terms stay in FP16's normal range; the block sums are scaled back exactly.
+template <bool TAN, bool GAIN>
+__global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per_eu(3))) void k_mix256(MixArgs a) {
+  constexpr int N = 256, M = 512, HW = GAIN ? 8 : 4;
+  constexpr int kWpg = TAN ? 2 : 1;           // wavefronts per workgroup
   constexpr int ROW = 18;                     // complex values per (E-W beam, k2) row: 16 a1 + 2 pad
-  __shared__ float4 lds_raw[2 * 32 * ROW / 2];
-  cf* const tile = reinterpret_cast<cf*>(lds_raw);
+  constexpr int NMU = 28;                     // floats per column of multipliers: 25, in 16-byte loads
+  static_assert(dit_slots(16) <= NMU, "multipliers");
+  __shared__ float4 lds_tiles[kWpg][2 * 32 * ROW / 2];
+  __shared__ __attribute__((aligned(16))) float lds_mu[TAN ? 32 : 1][NMU];
+  __shared__ __attribute__((aligned(16))) float lds_h[TAN ? N * HW : 4];
 
-  const int lane = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float4* const lds_raw = lds_tiles[wave];
+  cf* const tile = reinterpret_cast<cf*>(lds_raw);
   const int n = lane & 15, g = lane >> 4;
-  int wg = blockIdx.x;
+
+  // the weights, scaled by 2^-ex with 2^ex the power of two just above the
+  // largest component (every wavefront looks at them all)
+  int ex;
+  float hw[4][TAN ? 1 : HW];                  // at the lane's N-S positions n + 64 g + 16 i
+  {
+    float m = 0.f;
+    const float4* const h4 = reinterpret_cast<const float4*>(a.taper);
+#pragma unroll
+    for (int i = 0; i < N * HW / 256; ++i) {
+      const float4 v = h4[lane + 64 * i];
+      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+    }
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
+    ex = m > 0.f && m < INFINITY ? ilogbf(m) + 1 : 0;
+    if constexpr (TAN) {
+      for (int i = tid; i < N * HW; i += 64 * kWpg) lds_h[i] = ldexpf(a.taper[i], -ex);
+      for (int i = tid; i < 32 * dit_slots(16); i += 64 * kWpg)
+        lds_mu[i / dit_slots(16)][i % dit_slots(16)] = a.mult[i];
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int q = 0; q < HW; ++q) hw[i][q] = ldexpf(a.taper[HW * (n + 64 * g + 16 * i) + q], -ex);
+    }
+  }
+  if constexpr (TAN) __syncthreads();
+  const int64_t task = (int64_t)blockIdx.x * kWpg + wave;
+  if (task >= a.n_wg) return;
+  int wg = (int)task;
   const int pg = wg % a.n_pg;
   wg /= a.n_pg;
   const int chan = wg % a.n_chan;
@@ -135,11 +186,21 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
       for (int part = 0; part < 2; ++part)
         B1[p][kt][part] = *reinterpret_cast<const half8*>(
             tab + kH256B1Off + 2 * (p * 2048 + ((kt * 2 + part) * 64 + lane) * 8));
+  // twiddles of a1 = 4 g + q, k2 = 16 kt + n.  TAN: 1 + i t, in column 16
+  // pr + i t; else whole
+  float tt[2][4], pr[4];
   cf tw[2][4];
-  {
-    const float2* w = reinterpret_cast<const float2*>(tab + kH256TwOff) + lane * 8;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) tw[k >> 2][k & 3] = cf{w[k].x, w[k].y};
+  for (int k = 0; k < 8; ++k) {
+    const int kt = k >> 2, q = k & 3;
+    if constexpr (TAN) {
+      const float2 w = a.tw[(4 * g + q) * 32 + 16 * kt + n];
+      tt[kt][q] = kt && n == 0 ? w.y : w.x;
+      if (kt) pr[q] = n == 0 ? w.x : 1.f;
+    } else {
+      const float2 w = reinterpret_cast<const float2*>(tab + kH256TwOff)[lane * 8 + k];
+      tw[kt][q] = cf{w.x, w.y};
+    }
   }
   const int k2s = lane & 31, es = lane >> 5;  // stage-2 column and E-W beam within the pair
   float acc[2][16];
@@ -148,39 +209,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
 #pragma unroll
     for (int k = 0; k < 16; ++k) acc[p][k] = 0.f;
 
-  // the window at the lane's N-S positions n + 64 g + 16 i, scaled by 2^-E
-  // with 2^E the power of two just above the wavefront's largest |h|
-  float hw[4][4];
-  float unscale = 1.f;       // 2^{2E}: undoes the scale on |B|^2
-  {
-    float m = 0.f;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float4 v = *reinterpret_cast<const float4*>(a.taper + 4 * (n + 64 * g + 16 * i));
-      hw[i][0] = v.x;
-      hw[i][1] = v.y;
-      hw[i][2] = v.z;
-      hw[i][3] = v.w;
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
-    }
-#pragma unroll
-    for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
-    const int ex = m > 0.f ? ilogbf(m) + 1 : 0;      // m * 2^-ex in [1/2, 1)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) hw[i][q] = ldexpf(hw[i][q], -ex);
-    unscale = ldexpf(1.f, 2 * ex);
-  }
-
   const int pol_lo = (a.pol_iter == 1) ? pg : 0;
   const int pol_hi = (a.pol_iter == 1) ? pg + 1 : a.n_pol;
   const int64_t frame_stride = (int64_t)a.n_chan * a.n_pol * N;   // dwords per sample
   const int64_t t0 = (int64_t)blk * a.block;
 
   auto frame = [&](const uint32_t (&dw)[4]) {
-    float xw[4][8];
-    ew_windowed(dw, hw, xw);
+    cf xw[4][4];                              // [E-W beam][position]
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      cf b[4];
+      if constexpr (TAN) {
+        float h[HW];
+#pragma unroll
+        for (int v = 0; v < HW / 4; ++v) {
+          const float4 f = *reinterpret_cast<const float4*>(&lds_h[HW * (n + 64 * g + 16 * i) + 4 * v]);
+          h[4 * v] = f.x;
+          h[4 * v + 1] = f.y;
+          h[4 * v + 2] = f.z;
+          h[4 * v + 3] = f.w;
+        }
+        ew_weighted<GAIN>(dw[i], h, b);
+      } else {
+        ew_weighted<GAIN>(dw[i], hw[i], b);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xw[e][i] = b[e];
+    }
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
       // ---- stage 1 and twiddle for E-W beams 2p, 2p + 1, into the tile ----
@@ -190,22 +245,27 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
         f32x4 y[2][2];
         uint32_t hi[4], lo[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) split2(xw[e][2 * i], xw[e][2 * i + 1], hi[i], lo[i]);
+        for (int i = 0; i < 4; ++i) split2(xw[e][i].r, xw[e][i].i, hi[i], lo[i]);
         const half8 Ah = __builtin_bit_cast(half8, hi), Al = __builtin_bit_cast(half8, lo);
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
           for (int part = 0; part < 2; ++part) {
-            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, B1[0][kt][part], f32x4{0.f, 0.f, 0.f, 0.f},
+            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al, B1[0][kt][part], f32x4{0.f, 0.f, 0.f, 0.f},
                                                                  0, 0, 0);
             y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, B1[1][kt][part], y[kt][part], 0, 0, 0);
-            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al, B1[0][kt][part], y[kt][part], 0, 0, 0);
+            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, B1[0][kt][part], y[kt][part], 0, 0, 0);
           }
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
           cf z[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q) z[q] = cmul(cf{y[kt][0][q], y[kt][1][q]}, tw[kt][q]);
+          for (int q = 0; q < 4; ++q) {
+            const float yr = y[kt][0][q], yi = y[kt][1][q];
+            if constexpr (!TAN) z[q] = cmul(cf{yr, yi}, tw[kt][q]);
+            else if (kt == 0) z[q] = cf{fmaf(-tt[0][q], yi, yr), fmaf(tt[0][q], yr, yi)};
+            else z[q] = cf{fmaf(-tt[1][q], yi, pr[q] * yr), fmaf(tt[1][q], yr, pr[q] * yi)};
+          }
           float4* dst = reinterpret_cast<float4*>(&tile[(ep * 32 + 16 * kt + n) * ROW + 4 * g]);
           dst[0] = make_float4(z[0].r, z[0].i, z[1].r, z[1].i);
           dst[1] = make_float4(z[2].r, z[2].i, z[3].r, z[3].i);
@@ -223,8 +283,22 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
           x[2 * m + 1] = cf{v.z, v.w};
         }
       }
-      wave_lds_sync();
-      dit<16>(x);
+      if constexpr (TAN) {
+        float mu[NMU];
+#pragma unroll
+        for (int k = 0; k < NMU / 4; ++k) {
+          const float4 v = *reinterpret_cast<const float4*>(&lds_mu[k2s][4 * k]);
+          mu[4 * k] = v.x;
+          mu[4 * k + 1] = v.y;
+          mu[4 * k + 2] = v.z;
+          mu[4 * k + 3] = v.w;
+        }
+        wave_lds_sync();
+        dit_rs<16>(x, mu);
+      } else {
+        wave_lds_sync();
+        dit<16>(x);
+      }
 #pragma unroll
       for (int k1 = 0; k1 < 16; ++k1) acc[p][k1] = cnorm_acc(x[k1], acc[p][k1]);
     }
@@ -265,7 +339,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
   float* o = a.out + (((int64_t)blk * a.n_chan + chan) * a.n_pg + pg) * 4 * keep;
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    for (int j = lane; j < keep; j += 64) o[e * keep + j] = lds_i[e * M + (sel ? sel[j] : j)] * (a.norm * unscale);
+    for (int j = lane; j < keep; j += 64) o[e * keep + j] = ldexpf(lds_i[e * M + (sel ? sel[j] : j)] * a.norm, 2 * ex);
 }
 
 }  // namespace
@@ -277,10 +351,15 @@ hipError_t launch_mix256_tables(void* mat, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_mix256(const MixArgs& a, int64_t n_wg, hipStream_t s) {
+hipError_t launch_mix256(const MixArgs& a, bool fp32, int64_t n_wg, hipStream_t s) {
   if (n_wg == 0) return hipSuccess;
   if (n_wg > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(k_mix256, dim3((unsigned)n_wg), dim3(64), 0, s, a);
+  MixArgs b = a;
+  b.n_wg = n_wg;
+  const unsigned n2 = (unsigned)((n_wg + 1) / 2);
+  if (a.gains) hipLaunchKernelGGL((k_mix256<true, true>), dim3(n2), dim3(128), 0, s, b);
+  else if (fp32) hipLaunchKernelGGL((k_mix256<true, false>), dim3(n2), dim3(128), 0, s, b);
+  else hipLaunchKernelGGL((k_mix256<false, false>), dim3((unsigned)n_wg), dim3(64), 0, s, b);
   return hipGetLastError();
 }
 

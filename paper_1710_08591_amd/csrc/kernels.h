@@ -159,6 +159,12 @@ struct MixArgs {
   int n_chan, n_pol, n_pg, pol_iter, block;
   const void* mat;         // DFT operand tables (plan-owned)
   const float* taper;
+  // 4 x 256: whether taper holds complex gains [n_ns][4][2]; the plan's twiddle
+  // and multiplier tables (as Fft32Args); tasks (set by the launch)
+  bool gains;
+  const float2* tw;
+  const float* mult;
+  int64_t n_wg;
   const int32_t* sel;
   int n_keep;
   float* out;
@@ -174,6 +180,6 @@ bool mix_window_supported(int n_ns, int prec);
 // the 4 x 256 lattice (k_mix256.hip): stage 1 on the matrix cores, stage 2 in FP32
 size_t mix256_table_bytes();
 hipError_t launch_mix256_tables(void* mat, hipStream_t s);
-hipError_t launch_mix256(const MixArgs& a, int64_t n_wg, hipStream_t s);
+hipError_t launch_mix256(const MixArgs& a, bool fp32, int64_t n_wg, hipStream_t s);
 
 }  // namespace fftbf
