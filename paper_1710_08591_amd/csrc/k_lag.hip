@@ -135,7 +135,7 @@ constexpr int kLagLimit = 1 << 19;
 
 // One workgroup: four wavefronts, wavefront e owns E-W beam e.  256 / N tasks
 // (block, channel, polarisation group) at a time, two rounds per output.
-template <int N, bool LONG>
+template <int N, bool LONG, bool SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_lag(LagArgs p) {
   using sum_t = typename std::conditional<LONG, double, int>::type;
   constexpr int M = 2 * N;
@@ -155,14 +155,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int e = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // slot `sub` of the G side by side: steps sub_q, sub_q + parts, ... of task sub_t
+  const int parts = SPLIT ? p.parts : 1;
   const int sub = G == 1 ? 0 : tid / N, a = tid % N;
+  const int sub_t = SPLIT ? sub / parts : sub, sub_q = SPLIT ? sub - sub_t * parts : 0;
   v4i* const plane = lds_x + e * 512;        // read by wavefront e only
 
   for (int i = tid; i < NTW; i += 256) lds_tw[i] = p.tw[i];
   if (tid == 0) lds_x[2048] = v4i{0, 0, 0, 0};
 
   const int n_chunk = (p.block + 15) / 16;
-  const int n_step = n_chunk * p.pol_iter;
+  const int n_all = n_chunk * p.pol_iter, n_step = (n_all + parts - 1) / parts;
   const int64_t frame = (int64_t)p.n_chan * p.n_pol * N;     // dwords per sample
   const uint32_t n_task = (uint32_t)p.n_task, per_unit = p.tpi * p.iters;
   const uint32_t n_unit = (n_task + per_unit - 1) / per_unit;
@@ -176,11 +179,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
   };
   auto load = [&](uint32_t unit, int it, int step) {
     Raw w;
-    uint32_t task = unit * per_unit + it * p.tpi + sub;
-    if (task >= n_task || sub >= p.tpi) task = 0;
+    uint32_t task = unit * per_unit + it * p.tpi + sub_t;
+    if (task >= n_task || sub_t >= p.tpi) task = 0;
+    step = step * parts + sub_q;
+    if (SPLIT && step >= n_all) step = 0;
     const uint32_t pg = p.n_pg == 2 ? task & 1 : 0, rest = p.n_pg == 2 ? task >> 1 : task;
     const uint32_t blk = rest / (uint32_t)p.n_chan, chan = rest - blk * p.n_chan;
-    const int pi = p.pol_iter == 1 ? 0 : step / n_chunk;
+    const int pi = step >= n_chunk;          // at most two polarisations
     const int t0 = (step - pi * n_chunk) * 16, nt = p.block - t0;
     const uint32_t* src = p.volts + ((int64_t)blk * p.block + t0) * frame + ((int64_t)chan * p.n_pol + pg + pi) * N;
 #pragma unroll
@@ -191,10 +196,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     return w;
   };
   auto mask_step = [&](uint32_t unit, int it, int step, Raw w) {
-    const uint32_t task = unit * per_unit + it * p.tpi + sub;
-    const int pi = p.pol_iter == 1 ? 0 : step / n_chunk, nt = p.block - (step - pi * n_chunk) * 16;
-    if (nt < 16 || p.tpi < G || (unit + 1) * per_unit > n_task) {
-      const uint32_t live = (sub < p.tpi && task < n_task) ? ~0u : 0u;
+    const uint32_t task = unit * per_unit + it * p.tpi + sub_t;
+    step = step * parts + sub_q;
+    const int pi = step >= n_chunk, nt = p.block - (step - pi * n_chunk) * 16;
+    if (SPLIT || nt < 16 || p.tpi < G || (unit + 1) * per_unit > n_task) {
+      const uint32_t live = (sub_t < p.tpi && task < n_task && step < n_all) ? ~0u : 0u;
 #pragma unroll
       for (int t = 0; t < 16; ++t) w.v[t] &= t < nt ? live : 0u;
     }
@@ -284,7 +290,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int s0 = 0; s0 < G; s0 += GS) {
-          if (s0 >= p.tpi) break;
+          if (s0 >= p.tpi * parts) break;
 #pragma unroll
           for (int s = s0; s < s0 + GS; ++s) {
             // rows for the real parts [x_r, x_i] and the imaginary parts [-x_i, x_r]
@@ -350,6 +356,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
       }
     }
     wave_sync();
+    if constexpr (SPLIT) {
+      // the slots of a task become one
+      for (int k = lane; k < 4 * p.tpi * N; k += 64) {
+        const int arr = k / (p.tpi * N), r = k - arr * (p.tpi * N), t = r / N;
+        sum_t* const at = own + arr * 256 + r % N;
+        sum_t sum = at[t * parts * N];
+        for (int q = 1; q < parts; ++q) sum += at[(t * parts + q) * N];
+        wave_sync();                       // no slot is written before the lanes of this turn have read theirs
+        at[t * N] = sum;
+      }
+      wave_sync();
+    }
 
     // ---- M-point transforms, the two rounds' tasks as one complex series ----
     int fl_lane = lane;
@@ -493,17 +511,31 @@ template <int N>
 void launch_n(LagArgs a, hipStream_t s) {
   constexpr int G = 256 / N;
   constexpr int kWgs = 512;                 // two workgroups per compute unit
-  // few tasks: fewer per workgroup, so that they spread over the chip
-  int64_t per = a.n_task / kWgs;
-  if (per < 1) per = 1;
-  a.iters = per > 1 ? 2 : 1;
+  // few tasks: fewer per workgroup, so that they spread over the chip, and a
+  // second round only if one does not hold them
+  const int64_t per = (a.n_task + kWgs - 1) / kWgs;
+  a.iters = per > G ? 2 : 1;
   const int64_t tpi = (per + a.iters - 1) / a.iters;
   a.tpi = tpi < G ? (int)tpi : G;
+  // slots left over take every parts-th step of 16 samples each (SPLIT): one
+  // block of 1600 samples 141 -> 24 us at 4 x 16, 1.34 -> 0.13 ms at 4 x 128
+  // against one wavefront's transforms; 225 channels of 48 samples and two
+  // polarisations at 4 x 16 took 14.5 us with a slot each and 11.6 before
+  const int n_all = (a.block + 15) / 16 * a.pol_iter;
+  a.parts = G / a.tpi < n_all ? G / a.tpi : n_all;
   const int64_t pu = (int64_t)a.tpi * a.iters;
   const int64_t n_unit = (a.n_task + pu - 1) / pu;
   const dim3 grid((unsigned)(n_unit < kWgs ? n_unit : kWgs)), threads(256);
-  if ((int64_t)N * a.block * a.pol_iter < kLagLimit) hipLaunchKernelGGL((k_lag<N, false>), grid, threads, 0, s, a);
-  else hipLaunchKernelGGL((k_lag<N, true>), grid, threads, 0, s, a);
+  const bool fits = (int64_t)N * a.block * a.pol_iter < kLagLimit;
+  if constexpr (G > 1) {
+    if (a.parts > 1) {
+      if (fits) hipLaunchKernelGGL((k_lag<N, false, true>), grid, threads, 0, s, a);
+      else hipLaunchKernelGGL((k_lag<N, true, true>), grid, threads, 0, s, a);
+      return;
+    }
+  }
+  if (fits) hipLaunchKernelGGL((k_lag<N, false, false>), grid, threads, 0, s, a);
+  else hipLaunchKernelGGL((k_lag<N, true, false>), grid, threads, 0, s, a);
 }
 
 }  // namespace

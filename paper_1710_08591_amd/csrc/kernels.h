@@ -60,7 +60,7 @@ struct LagArgs {
   int n_keep;
   float* out;
   float norm;              // 1 / (n_ew n_ns)
-  int tpi, iters;          // tasks per round and rounds of a workgroup's unit (set by the launch)
+  int tpi, iters, parts;   // tasks per round, rounds of a workgroup's unit, slots per task (set by the launch)
 };
 // doubles pairs of the twiddle table of an m-point transform
 constexpr int lag_tw_count(int m) { return 7 * (m / 8) + (m > 64 ? 7 * (m / 64) : 0); }
