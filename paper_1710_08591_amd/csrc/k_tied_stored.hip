@@ -17,14 +17,15 @@
 // and reads, splits and multiplies each beam once for all PT tiles.
 //
 // 4 x 64, 32 channels, 2 polarisations, 2048 samples, 48 pointings: 537 MB of
-// beams in 163 us (3.3 TB/s); the same contraction on v_mfma_f32_16x16x4_f32,
+// beams in 178 us (3.0 TB/s); the same contraction on v_mfma_f32_16x16x4_f32,
 // one tile of 16 pointings per workgroup, took 404 us, bound by the FP32
 // matrix rate (179 us) and by reading the beams three times.  The products
 // take about 70 us here and the reads about 110: neither fills its unit, the
-// splits (7 instructions per complex value and term pair) run between them.
-// Against 64 bits the errors are smaller than before (2-norm of the beams
-// 2.2e-7 against 2.3e-7 at M = 128, 3.6e-7 against 4.4e-7 at 512): fewer
-// roundings of the partial sums.
+// splits (14 instructions per complex value) run between them.  Each chunk's
+// products are summed by themselves before they join the running sum: 15 us,
+// and errors against 64 bits a third of the FP32 instructions' (2-norm of the
+// beams 0.84e-7 against 2.3e-7 at M = 128, 1.2e-7 against 4.4e-7 at 512; in one
+// chain 2.2e-7 and 3.6e-7, larger than the FP32 instructions' on some inputs).
 
 #include "dev_bf16.h"
 #include "dev_common.h"
@@ -99,7 +100,7 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
   float bad = 0.f;
   constexpr int D = 2;             // chunks loaded ahead
   f32x4 ring[D + 1][2];
-  static_assert(NC % 4 == 0 || NC == 2, "chunks");
+  static_assert(NC % 4 == 0, "chunks");
   const float* bp = quad_ptr(pol_lo, 4 * sub);
 #pragma unroll
   for (int k = 0; k < D; ++k)
@@ -115,7 +116,7 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
       f32x4 zr[PT], zi[PT];
 #pragma unroll
       for (int pt = 0; pt < PT; ++pt) zr[pt] = zi[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      constexpr int UN = NC % 4 == 0 ? 4 : NC;
+      constexpr int UN = NC > 4 ? 4 : NC / 2;      // (whole quads unrolled spill)
 #pragma unroll 1
       for (int k0 = 0; k0 < NC; k0 += UN) {
 #pragma unroll
@@ -167,8 +168,11 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
 #pragma unroll
             for (int pt = 0; pt < PT; ++pt) {
               const u32x4 w[3] = {lds.w[pt][kc][0][lane], lds.w[pt][kc][1][lane], lds.w[pt][kc][2][lane]};
-              zr[pt] = mfma_bf16x3(w, dr, zr[pt]);
-              zi[pt] = mfma_bf16x3(w, di, zi[pt]);
+              // the chunk's products by themselves: two roundings of the running sum's size, not six
+              const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+              const f32x4 cr = mfma_bf16x3(w, dr, none), ci = mfma_bf16x3(w, di, none);
+              zr[pt] += cr;
+              zi[pt] += ci;
             }
           }
         }
@@ -301,15 +305,19 @@ hipError_t launch_mp(TiedArgs a, hipStream_t s) {
   const int slots = kTsWaves / a.unit_split;
   // The number of runs that ends soonest: rounds of resident workgroups times a
   // run's turns of its wavefronts, and the weights that each workgroup makes
-  // first (about a third of a turn of whole units).
+  // first (about a third of a turn of whole units).  Only the most runs that fit
+  // a number of rounds are worth a look.
   constexpr int kWgs = sizeof(TsLds<M, PT>) > 80 * 1024 ? 256 : 512;
   const int64_t max_runs = (n_unit + slots - 1) / slots;
   int64_t runs = 1;
   double best = 0.0;
-  for (int64_t r = 1; r <= max_runs && (r == 1 || base * (r - 1) < 4 * kWgs); ++r) {
+  for (int k = 0; k < 5; ++k) {
+    const int64_t rounds = (base + kWgs - 1) / kWgs + k;
+    int64_t r = rounds * kWgs / base;
+    if (r > max_runs) r = max_runs;
     const int64_t turns = ((n_unit + r - 1) / r + slots - 1) / slots;
     const double cost = (double)((base * r + kWgs - 1) / kWgs) * ((double)turns + 0.3 * a.unit_split);
-    if (r == 1 || cost < best) {
+    if (k == 0 || cost < best) {
       best = cost;
       runs = r;
     }
