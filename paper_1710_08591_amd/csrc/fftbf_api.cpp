@@ -261,7 +261,13 @@ static bf_status beamform_fft_impl(const bf_plan* plan, const uint8_t* volts, in
   if (n_wg > 0x7FFFFFFFLL) return fail(BF_ERR_UNSUPPORTED, "beamform_fft: grid too large, split the call");
   hipError_t e;
   const int pol_iter = (n_pg == 1) ? d.n_pol : 1;
-  if (kind == BF_OUT_INTENSITY && !taper && plan->lag) {
+  // The 4 x 16 lattice's FP16 plans keep their dense 16-point products where
+  // short blocks leave the stacked visibilities an FP64 transform per few
+  // samples: 256 channels, 2 polarisations, 1024 blocks of 16 samples 308 us
+  // against 327, 256 summed 67 against 77, blocks of 48 44 against 46; blocks of
+  // 80 128 against 124, and few tasks leave them too few wavefronts.
+  const bool dense16 = d.precision == BF_PREC_FP16_MFMA && d.n_ns == 16 && d.block <= 64 && n_wg >= 4096;
+  if (kind == BF_OUT_INTENSITY && !taper && plan->lag && !dense16) {
     fftbf::LagArgs a{};
     a.volts = reinterpret_cast<const uint32_t*>(volts);
     a.n_task = n_wg;

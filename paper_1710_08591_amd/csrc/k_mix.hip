@@ -1,6 +1,6 @@
-// Windowed FP16 FFT beamformer on the matrix cores (gfx950): intensities of
-// FP16 plans with real per-antenna weights.  (Unwindowed intensities of every
-// precision take the stacked visibilities of k_lag.hip.)
+// FP16 FFT beamformer on the matrix cores (gfx950): intensities of FP16 plans
+// with real per-antenna weights, and on the 4 x 16 lattice without.  (Other
+// unwindowed intensities take the stacked visibilities of k_lag.hip.)
 //
 // On the 4 x 16 lattice the N-S transform is one dense, zero-padded DFT (16
 // non-zero inputs -> M = 32 beams; eq. e:fftbeamform with the weights of eq.
@@ -66,12 +66,50 @@ __device__ __forceinline__ f32x4 mfma(half8 a, half8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// Per-antenna real weights h[a_ns][a_ew] (Sec. "Controlling beam shape with
+// dot8 weights for component comp (0 Re, 1 Im) of E-W beam e:
+// sum_q x_q (-i)^{e q}; nibble 2q+1 is Re(x_q), nibble 2q is Im(x_q)
+__device__ __forceinline__ int ew_dot_weights(int e, int comp) {
+  int wre = 0, wim = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int k = (e * q) & 3;
+    const int sr = 4 * (2 * q + 1), si = 4 * (2 * q);
+    if (k == 0) { wre |= 1 << sr;   wim |= 1 << si; }
+    if (k == 1) { wre |= 1 << si;   wim |= 0xF << sr; }
+    if (k == 2) { wre |= 0xF << sr; wim |= 0xF << si; }
+    if (k == 3) { wre |= 0xF << si; wim |= 1 << sr; }
+  }
+  return comp ? wim : wre;
+}
+
+// The E-W sums x (|x| <= 32) of eight dwords as FP16, without conversion
+// instructions: the dot product starts from 0x6600, the FP16 pattern of
+// 1536, whose unit step is 1, so the low half of 0x6600 + x is exactly
+// FP16(1536 + x); two are packed and 1536 comes off in one packed FP16
+// subtraction (exact).
+__device__ __forceinline__ half8 ew_sums_f16(const uint32_t* dw, int w) {
+  half8 A;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const uint32_t lo = (uint32_t)sdot8_acc((int)dw[2 * j], w, 0x6600);
+    const uint32_t hi = (uint32_t)sdot8_acc((int)dw[2 * j + 1], w, 0x6600);
+    const half2 v = __builtin_bit_cast(half2, __builtin_amdgcn_perm(hi, lo, 0x05040100u)) -
+                    half2{(_Float16)1536.0f, (_Float16)1536.0f};
+    A[2 * j] = v[0];
+    A[2 * j + 1] = v[1];
+  }
+  return A;
+}
+
+// WIN: per-antenna real weights h[a_ns][a_ew] (Sec. "Controlling beam shape with
 // windowing").  The windowed E-W sums are not integers, so each is split into
 // FP16 hi + lo; the window is scaled per wavefront by a power of two so that
 // its largest weight lies in [1/2, 1), and the block sums are scaled back
 // exactly.
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_mix16(MixArgs a) {
+// Without a window the E-W sums are integers that FP16 holds exactly: one data
+// term, two products.
+template <bool WIN>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(WIN ? 4 : 6))) void k_mix16(MixArgs a) {
   __shared__ float lds_i[4 * 32];
 
   const int lane = threadIdx.x;
@@ -92,6 +130,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 #pragma unroll
       for (int part = 0; part < 2; ++part) B[p][kt][part] = load_b(a.mat, p, kt, part, lane);
 
+  int wts[4];                                 // E-W dot8 weights of this lane's component
+#pragma unroll
+  for (int e = 0; e < 4; ++e) wts[e] = ew_dot_weights(e, g >> 1);
   const int pol_lo = (a.pol_iter == 1) ? pg : 0;
   const int pol_hi = (a.pol_iter == 1) ? pg + 1 : a.n_pol;
   const int keep = a.n_keep;
@@ -108,9 +149,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
   // the window at the lane's N-S positions 8 (g & 1) + j, scaled by 2^-E with
   // 2^E the power of two just above the wavefront's largest |h|
-  float hw[8][4];
+  float hw[WIN ? 8 : 1][4];
   float unscale = 1.f;       // 2^{2E}: undoes the scale on |B|^2
-  {
+  if constexpr (WIN) {
     float m = 0.f;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -147,39 +188,61 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         const uint4 d1 = fr[2 * (g & 1) + 1];
         const uint32_t dw[8] = {d0.x, d0.y, d0.z, d0.w, d1.x, d1.y, d1.z, d1.w};
 
-        // windowed E-W sums of every E-W beam at the lane's eight positions,
-        // the lane's component of each, split into FP16 hi + lo
-        float xw[4][8];
+        if constexpr (WIN) {
+          // windowed E-W sums of every E-W beam at the lane's eight positions,
+          // the lane's component of each, split into FP16 hi + lo
+          float xw[4][8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          cf w[4];
+          for (int j = 0; j < 8; ++j) {
+            cf w[4];
 #pragma unroll
-          for (int q = 0; q < 4; ++q)
-            w[q] = cf{hw[j][q] * (float)(int)__builtin_amdgcn_sbfe((int)dw[j], 8 * q + 4, 4),
-                      hw[j][q] * (float)(int)__builtin_amdgcn_sbfe((int)dw[j], 8 * q, 4)};
-          const cf s02 = cadd(w[0], w[2]), d02 = csub(w[0], w[2]), s13 = cadd(w[1], w[3]), d13 = csub(w[1], w[3]);
-          const cf be[4] = {cadd(s02, s13), cf{d02.r + d13.i, d02.i - d13.r}, csub(s02, s13),
-                            cf{d02.r - d13.i, d02.i + d13.r}};
+            for (int q = 0; q < 4; ++q)
+              w[q] = cf{hw[j][q] * (float)(int)__builtin_amdgcn_sbfe((int)dw[j], 8 * q + 4, 4),
+                        hw[j][q] * (float)(int)__builtin_amdgcn_sbfe((int)dw[j], 8 * q, 4)};
+            const cf s02 = cadd(w[0], w[2]), d02 = csub(w[0], w[2]), s13 = cadd(w[1], w[3]), d13 = csub(w[1], w[3]);
+            const cf be[4] = {cadd(s02, s13), cf{d02.r + d13.i, d02.i - d13.r}, csub(s02, s13),
+                              cf{d02.r - d13.i, d02.i + d13.r}};
 #pragma unroll
-          for (int e = 0; e < 4; ++e) xw[e][j] = im_lane ? be[e].i : be[e].r;
-        }
+            for (int e = 0; e < 4; ++e) xw[e][j] = im_lane ? be[e].i : be[e].r;
+          }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          uint32_t hi[4], lo[4];
+          for (int e = 0; e < 4; ++e) {
+            uint32_t hi[4], lo[4];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) split2(xw[e][2 * j], xw[e][2 * j + 1], hi[j], lo[j]);
-          const half8 Ah = __builtin_bit_cast(half8, hi), Al = __builtin_bit_cast(half8, lo);
+            for (int j = 0; j < 4; ++j) split2(xw[e][2 * j], xw[e][2 * j + 1], hi[j], lo[j]);
+            const half8 Ah = __builtin_bit_cast(half8, hi), Al = __builtin_bit_cast(half8, lo);
 #pragma unroll
-          for (int kt = 0; kt < 2; ++kt) {
-            f32x4 y[2];
+            for (int kt = 0; kt < 2; ++kt) {
+              f32x4 y[2];
 #pragma unroll
-            for (int part = 0; part < 2; ++part) {
-              y[part] = mfma(Ah, B[0][kt][part], f32x4{0.f, 0.f, 0.f, 0.f});
-              y[part] = mfma(Ah, B[1][kt][part], y[part]);
-              y[part] = mfma(Al, B[0][kt][part], y[part]);
+              for (int part = 0; part < 2; ++part) {
+                y[part] = mfma(Ah, B[0][kt][part], f32x4{0.f, 0.f, 0.f, 0.f});
+                y[part] = mfma(Ah, B[1][kt][part], y[part]);
+                y[part] = mfma(Al, B[0][kt][part], y[part]);
+              }
+#pragma unroll
+              for (int i = 0; i < 4; ++i) ia[e][kt] = cnorm_acc(cf{y[0][i], y[1][i]}, ia[e][kt]);
             }
+          }
+        } else {
+          // FP16 holds the E-W sums exactly, so the E-W DFT goes first (as
+          // signed 4-bit dot products on the packed bytes) and each E-W
+          // beam's N-S products land straight in its |B|^2
 #pragma unroll
-            for (int i = 0; i < 4; ++i) ia[e][kt] = cnorm_acc(cf{y[0][i], y[1][i]}, ia[e][kt]);
+          for (int e = 0; e < 4; ++e) {
+            const half8 A = ew_sums_f16(dw, wts[e]);
+#pragma unroll
+            for (int kt = 0; kt < 2; ++kt) {
+              f32x4 y[2];
+#pragma unroll
+              for (int part = 0; part < 2; ++part) {
+                y[part] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int p = 0; p < 2; ++p) y[part] = mfma(A, B[p][kt][part], y[part]);
+              }
+#pragma unroll
+              for (int i = 0; i < 4; ++i) ia[e][kt] = cnorm_acc(cf{y[0][i], y[1][i]}, ia[e][kt]);
+            }
           }
         }
       }
@@ -447,7 +510,7 @@ hipError_t launch_mix_tables(void* mat, int n_ns, hipStream_t s) {
 }
 
 hipError_t launch_mix(const MixArgs& a, int n_ns, int64_t n_wg_blocks, hipStream_t s) {
-  if (!a.taper || !mix_supported(n_ns, kPrecFp16, a.block)) return hipErrorNotSupported;
+  if (!mix_supported(n_ns, kPrecFp16, a.block) || (!a.taper && n_ns != 16)) return hipErrorNotSupported;
   if (n_ns == 256) return launch_mix256(a, false, n_wg_blocks, s);
   const int64_t n_blk = a.n_time / a.block;
   const int64_t n_run = (n_blk + kMixBlocksPerWave - 1) / kMixBlocksPerWave;
@@ -456,7 +519,10 @@ hipError_t launch_mix(const MixArgs& a, int n_ns, int64_t n_wg_blocks, hipStream
   if (n_wg > 0x7FFFFFFF) return hipErrorInvalidConfiguration;
   const dim3 grid((unsigned)n_wg), threads(64);
   switch (n_ns) {
-    case 16: hipLaunchKernelGGL(k_mix16, grid, threads, 0, s, a); break;
+    case 16:
+      if (a.taper) hipLaunchKernelGGL(k_mix16<true>, grid, threads, 0, s, a);
+      else hipLaunchKernelGGL(k_mix16<false>, grid, threads, 0, s, a);
+      break;
     case 32: hipLaunchKernelGGL(k_mixp<2>, grid, threads, 0, s, a); break;
     case 64: hipLaunchKernelGGL(k_mixp<4>, grid, threads, 0, s, a); break;
     case 128: hipLaunchKernelGGL(k_mixp<8>, grid, threads, 0, s, a); break;
