@@ -26,8 +26,8 @@ sys.path.insert(0, ROOT)
 METRIC = "beamformed antenna-samples/s FP32 FFT vs FP16/FP8-MFMA; %HBM peak; tied-beam p99 ms"
 HBM_PEAK_GBS = 8000.0
 FP32_VECTOR_PEAK_TFLOPS = 157.3
-FP16_MFMA_PEAK_TFLOPS = 2500.0
-FP32_MFMA_PEAK_TFLOPS = 157.3
+BF16_MFMA_PEAK_TFLOPS = 2500.0
+INT8_MFMA_PEAK_TOPS = 5000.0
 N_SIMD = 256 * 4       # 256 compute units x 4 SIMDs
 CLOCK_HZ = 2.4e9        # peak engine clock
 
@@ -298,7 +298,9 @@ def _time_launches(fn, n: int, warmup: int = 2, each: list = None, warm_ms: floa
 
 
 def run_chime_mixed(dev, w, volts, fp32_ms: float, checks: OracleChecks) -> dict:
-    """The same resident CHIME-shaped voltages through the FP16-MFMA plan."""
+    """The same resident CHIME-shaped voltages through the FP16 and FP8 plans
+    (unwindowed intensities of every precision are the same exact integer sums)
+    and with a window or gains."""
     import numpy as np
     import torch
 
@@ -319,20 +321,15 @@ def run_chime_mixed(dev, w, volts, fp32_ms: float, checks: OracleChecks) -> dict
                    v=sg.volts(w, blk * 16, 16, chans=[c], pols=[p]), m_ew=w.m_ew, m_ns=w.m_ns,
                    index=(0, 0, 0), sel=sel[c])
     alg = w.n_time * w.n_chan * w.n_pol * w.frame_bytes + out.numel() * 4
-    # the FP8 matrix-core plan on the same voltages (exact first-stage E-W sums, three stacked e4m3 terms)
+    # the FP8 plan on the same voltages
     plan8 = bf.Plan(n_ew=w.n_ew, n_ns=w.n_ns, m_ew=w.m_ew, m_ns=w.m_ns, n_pol=w.n_pol, n_chan=w.n_chan,
                     block=w.block, ns_select=w.ns_select(), d_over_lambda=w.d_over_lambda(),
                     precision=bf.BF_PREC_FP8_MFMA)
     ms8 = _time_launches(lambda: bf.beamform_fft(plan8, volts, out=out), 5)
     plan8.close()
-    # per frame: 4 E-W columns x 2 beam tiles x (Re, Im) of v_mfma_scale_f32_16x16x128_f8f6f4
-    mf8 = w.n_time * w.n_chan * w.n_pol * 4 * 2 * 2 * (16 * 16 * 128 * 2)
-    fp8_rec = {"precision": "fp8 (e4m3) mfma for stage 1 (exact first-stage E-W sums x0 +- x2, x1 +- x3, three "
-                            "coefficient terms stacked along K = 128); second E-W stage, twiddle and 16-point "
-                            "stage 2 in fp32",
+    fp8_rec = {"precision": "stacked visibilities as exact int8 products, FP64 transforms per block",
                "kernel_ms": ms8, "antenna_samples_per_s": w.antenna_samples / (ms8 / 1e3),
-               "speedup_vs_fp32": fp32_ms / ms8,
-               "mfma_tflops": mf8 / (ms8 / 1e3) / 1e12, "mfma_frac_of_fp8_peak": mf8 / (ms8 / 1e3) / 1e12 / 5000.0}
+               "speedup_vs_fp32": fp32_ms / ms8}
     checks.add_blocks(fp8_rec, "max_rel_power_err_sampled", out, w)
     # the per-antenna Gaussian window on the FP16 matrix-core plan (windowed E-W sums split into hi + lo)
     hwin = np.ascontiguousarray(sg.gaussian_taper(w.n_ew, w.n_ns), dtype=np.float32)
@@ -373,19 +370,18 @@ def run_chime_mixed(dev, w, volts, fp32_ms: float, checks: OracleChecks) -> dict
                    v=sg.volts(w, blk * 16, 16, chans=[c], pols=[p]), m_ew=w.m_ew, m_ns=w.m_ns,
                    index=(0, 0, 0), sel=sel[c], taper=np.asarray(h, dtype=np.float64))
     plan32.close()
-    # MFMA work issued per sample frame: 4 E-W beams x 2 beam tiles x (Re, Im) x 2 coefficient terms of
-    # v_mfma_f32_16x16x32_f16 (16 x 16 x 32 multiply-adds, 2 flop each)
+    # int8 matrix products issued: per 16 samples and E-W beam 160 of v_mfma_i32_16x16x64_i8 (the upper half of
+    # the 256 x 256 products in 16 x 16 tiles, real and imaginary parts)
     frames = w.n_time * w.n_chan * w.n_pol
-    mfma_flops = frames * 4 * 2 * 2 * 2 * (16 * 16 * 32 * 2)
+    mfma_ops = frames / 16 * 4 * 160 * (16 * 16 * 64 * 2)
     plan.close()
     rec.update({"workload": "same as the headline (4x256, 2 pol, 256 chan, 16384 samples, clamp 256)",
-                "precision": "fp16 mfma for stage 1 of 512 = 32 x 16 (exact int E-W sums, two-term coefficients, fp32 "
-                             "accumulation); twiddle and 16-point stage 2 in fp32",
+                "precision": "stacked visibilities as exact int8 products, FP64 transforms per block",
                 "kernel_ms": ms, "antenna_samples_per_s": w.antenna_samples / (ms / 1e3),
                 "speedup_vs_fp32": fp32_ms / ms,
                 "hbm_alg_gbs": alg / (ms / 1e3) / 1e9, "hbm_frac": alg / (ms / 1e3) / 1e9 / HBM_PEAK_GBS,
-                "mfma_tflops": mfma_flops / (ms / 1e3) / 1e12,
-                "mfma_frac_of_fp16_peak": mfma_flops / (ms / 1e3) / 1e12 / FP16_MFMA_PEAK_TFLOPS,
+                "mfma_int8_tops": mfma_ops / (ms / 1e3) / 1e12,
+                "mfma_frac_of_int8_peak": mfma_ops / (ms / 1e3) / 1e12 / INT8_MFMA_PEAK_TOPS,
                 "fp8_mfma": fp8_rec, "fp16_mfma_with_real_window": fp16_window_rec,
                 "fp32_with_complex_gains": gains_rec, "fp32_with_real_window": window_rec})
     return rec
@@ -569,16 +565,16 @@ def run_chime_regrid(dev, w, volts, fp32_ms: float, checks: OracleChecks, n_targ
                                   f"regridding to {n_target} pointings per channel, pol and block",
                       "fft_m_ew8_ms": fft8_ms, "fft_m_ew8_vs_headline": fft8_ms / fp32_ms,
                       "fft_m_ew8_gaussian_window": win8, "kernel_ms": r2_ms,
-                      "mfma_fp32_tflops": flops2 / (r2_ms / 1e3) / 1e12,
-                      "mfma_fp32_frac": flops2 / (r2_ms / 1e3) / 1e12 / FP32_MFMA_PEAK_TFLOPS})
+                      "contraction_tflops": flops2 / (r2_ms / 1e3) / 1e12,
+                      "mfma_bf16_frac": 6 * flops2 / (r2_ms / 1e3) / 1e12 / BF16_MFMA_PEAK_TFLOPS})
     rg2.close()
     plan8.close()
     del fft8, out2
     rec.update({"workload": "same voltages as the headline, no clamp (512 N-S beams), regridded to "
                             f"{n_target} sin(theta) targets per E-W beam, channel and block",
                 "fft_unclamped_ms": fft_ms, "kernel_ms": ms,
-                "mfma_fp32_tflops": flops / (ms / 1e3) / 1e12,
-                "mfma_fp32_frac": flops / (ms / 1e3) / 1e12 / FP32_MFMA_PEAK_TFLOPS,
+                "contraction_tflops": flops / (ms / 1e3) / 1e12,
+                "mfma_bf16_frac": 6 * flops / (ms / 1e3) / 1e12 / BF16_MFMA_PEAK_TFLOPS,
                 "hbm_alg_gbs": alg / (ms / 1e3) / 1e9, "hbm_frac": alg / (ms / 1e3) / 1e9 / HBM_PEAK_GBS,
                 "optimal_window_half_sine": windowed,
                 "localisation": localisation,
@@ -594,7 +590,7 @@ def run_extras(dev, checks: OracleChecks) -> dict:
     import paper_1710_08591_amd as bf
     import synthgen as sg
     ex = {}
-    # (1) FP32 FFT vs FP16 / FP8 MFMA on the 4 x 16 lattice at scale
+    # (1) FP32, FP16 and FP8 plans on the 4 x 16 lattice at scale
     w = sg.Workload("lattice4x16_scaled", 4, 16, 256, 2, 16384, 4, 32, 16, 6,
                     src_dircos=((0.3, -0.2), (-0.7, 0.5)), src_snr=(10.0, 30.0), dl_lo=0.4, dl_hi=0.8)
     volts = sg.volts(w, backend="torch", device=dev)
@@ -613,11 +609,6 @@ def run_extras(dev, checks: OracleChecks) -> dict:
         for b, c, p in picks:
             checks.add(variants[name], "max_rel_power_err_sampled", "fft_rel", out[b, c, p].cpu().numpy(),
                        v=sg.volts(w, b * 16, 16, chans=[c], pols=[p]), m_ew=4, m_ns=32, index=(0, 0, 0))
-        if prec:
-            # MFMA work actually issued: N-S DFT as [64 x 32] real matrix per E-W column, per term
-            terms = 2 if prec == 1 else 3
-            mf = w.n_time * w.n_chan * w.n_pol * 4 * 64 * 32 * 2 * terms
-            variants[name]["mfma_tflops"] = mf / (ms / 1e3) / 1e12
         plan.close()
         del out
     ex["precision_variants"] = {"workload": "4x16 lattice, 2 pol, 256 chan, 16384 samples (512 MiB int4+4), "
@@ -641,7 +632,7 @@ def run_extras(dev, checks: OracleChecks) -> dict:
     ms = _time_launches(lambda: bf.form_tied_beams_v(plan, vt, 0, 256, d), 5, warmup=1)
     ex["tied_beams_v"] = {"workload": "4x16 lattice, 256 chan, 16384 samples, 64 pointings, |B|^2 over 16",
                           "kernel_ms": ms, "beam_samples_per_s": 64 * 256 * 16384 / (ms / 1e3)}
-    # the same tied beams interpolated from stored complex FFT beams (k_tied, FP32 vector ALUs)
+    # the same tied beams interpolated from stored complex FFT beams
     beams = bf.beamform_fft(plan, vt, kind=bf.BF_OUT_COMPLEX)
     ms_b = _time_launches(lambda: bf.form_tied_beams(plan, beams, 0, 256, d), 5, warmup=1)
     ex["tied_beams_from_fft_beams"] = {"workload": "same, from the stored complex 4 x 32 FFT beams "
@@ -674,7 +665,7 @@ def run_extras(dev, checks: OracleChecks) -> dict:
 
 
 def run_larger_lattices(dev, checks: OracleChecks) -> dict:
-    """FP32 vs FP16 / FP8 matrix cores (polyphase split) on the 4 x 64 and
+    """FP32, FP16 and FP8 plans on the 4 x 64 and
     4 x 128 lattices at the CHIME channel count and duration, and tied beams
     on the 4 x 256 lattice from voltages (FFT beams through a workspace) and
     from stored complex beams, each with sampled outputs for the oracle."""
@@ -730,9 +721,10 @@ def run_larger_lattices(dev, checks: OracleChecks) -> dict:
     beams = ws.view(torch.complex64)[: wt.n_time * 16 * 4 * 512].view(wt.n_time, 16, 1, 4, 512)
     bf.beamform_fft(plan, vt, kind=bf.BF_OUT_COMPLEX, out=beams)
     ms_b = _time_launches(lambda: bf.form_tied_beams(plan, beams, 0, 16, d, out=out), 5)
-    tb = {"workload": "the same, from the stored complex 4 x 512 FFT beams (FP32 matrix cores)",
+    tb = {"workload": "the same, from the stored complex 4 x 512 FFT beams (FP32 operands as three BF16 terms on the "
+                      "matrix cores)",
           "kernel_ms": ms_b, "beam_samples_per_s": n_bs / (ms_b / 1e3),
-          "mfma_fp32_tflops": n_bs * 8 * 4 * 512 / (ms_b / 1e3) / 1e12}
+          "contraction_tflops": n_bs * 8 * 4 * 512 / (ms_b / 1e3) / 1e12}
     for b, c in [(wt.n_time // 16 - 1, 15)]:
         checks.add(tb, "max_rel_power_err_sampled", "tied_rel", out[b, c].cpu().numpy(),
                    v=sg.volts(wt, 16 * b, 16, chans=[c]), dircos=dirs, dl=dl, c=c)
@@ -933,8 +925,8 @@ def main():
     in_bytes = w.n_time * w.n_chan * w.n_pol * w.frame_bytes
     out_bytes = out.numel() * 4
     alg_bytes = in_bytes + out_bytes
-    src_hash = kernel_source_hash("k_fft32.hip", "dev_common.h")
-    prof = counters_from_profile("traffic_fft32_chime.json", src_hash)
+    src_hash = kernel_source_hash("k_lag.hip", "dev_bytes.h")
+    prof = counters_from_profile("traffic_lag_chime.json", src_hash)
     traffic = prof.get("hbm_bytes_per_launch")
     # vector instructions issued per SIMD and clock cycle (counted
     # instructions over the live launch time, at the peak clock)
@@ -961,7 +953,8 @@ def main():
         "roofline": {"bound": "alu", "achieved": achieved_tflops, "peak": FP32_VECTOR_PEAK_TFLOPS,
                      "unit": "TFLOP/s", "frac": achieved_tflops / FP32_VECTOR_PEAK_TFLOPS,
                      "traffic": traffic,
-                     "kernel": "k_fft32_h (4 x 256, half-size tiles)", "kernel_ms": ms_avg,
+                     "kernel": "k_lag<256> (stacked visibilities; achieved counts the FFT's nominal flops)",
+                     "kernel_ms": ms_avg,
                      "kernel_ms_p10_p50_p90": [float(np.percentile(kern_ms, q)) for q in (10, 50, 90)],
                      "valu_insts_per_launch": valu,
                      "valu_insts_per_simd_cycle": valu_rate,

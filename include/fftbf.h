@@ -50,9 +50,10 @@ typedef enum {
 } bf_status;
 
 typedef enum {
-  BF_PREC_FP32 = 0,       /* FP32 radix FFT on the vector ALUs            */
-  BF_PREC_FP16_MFMA = 1,  /* N-S DFT stages on FP16 MFMA, FP32 accumulate */
-  BF_PREC_FP8_MFMA = 2    /* N-S DFT stages on FP8 MFMA, FP32 accumulate  */
+  BF_PREC_FP32 = 0,       /* every output and option                       */
+  BF_PREC_FP16_MFMA = 1,  /* intensities; with a window, N-S DFT stages on
+                             FP16 MFMA, FP32 accumulate                    */
+  BF_PREC_FP8_MFMA = 2    /* intensities without a window                  */
 } bf_precision;
 
 typedef enum {
@@ -127,12 +128,15 @@ bf_status bf_plan_get_desc(const bf_plan *plan, bf_plan_desc *desc);
  *          ns_select[chan][j], j < n_ns_keep, in that order.
  *          BF_OUT_COMPLEX (FP32 plans only): out is float2
  *            [n_time][n_chan][n_pol][m_ew][m_ns], every beam, unclamped.
- * The mixed-precision plans take the int4 samples exactly into FP16 / FP8
- * operands and round the DFT coefficients (split into a high and a low
- * part) to the working precision, accumulating in FP32; they produce
- * intensities only.  With a taper, FP16 plans split the windowed E-W sums
- * into FP16 high and low parts (taper 16-byte aligned); FP8 plans return
- * BF_ERR_UNSUPPORTED.  Mixed-precision plans need 16-byte aligned volts.
+ * Intensities without a taper (m_ns = 2 n_ns, m_ew = 4) come from the block's
+ * stacked visibilities (eq. e:b_V_delta), exact integer sums of the int4
+ * samples, transformed in FP64 and rounded once to float, in plans of every
+ * precision (FP16 plans of the 4 x 16 lattice keep products of the exact E-W
+ * sums with two-term FP16 coefficients, FP32 sums, for short blocks).  FP16
+ * and FP8 plans produce intensities only.  With a taper
+ * (16-byte aligned), FP16 plans split the windowed E-W sums and the DFT
+ * coefficients into FP16 high and low parts, accumulating in FP32; FP8 plans
+ * return BF_ERR_UNSUPPORTED.  FP16 and FP8 plans need 16-byte aligned volts.
  */
 bf_status bf_beamform_fft(const bf_plan *plan, const uint8_t *volts, int64_t n_time,
                           const float *taper, int32_t kind, void *out, void *stream);
@@ -176,8 +180,10 @@ bf_status bf_form_tied_beams(const bf_plan *plan, const void *fft_beams, int64_t
                              int32_t n_point, int32_t kind, void *out, void *stream);
 
 /*
- * Tied-array beams straight from voltages: the FFT beams of each sample are
- * formed on chip (FP32, as bf_beamform_fft) and interpolated as in
+ * Tied-array beams straight from voltages.  Without a taper the intensity of
+ * each pointing is a sum over the block's stacked visibilities on both axes
+ * (exact integers), with weights generated in FP64; with a taper the FFT
+ * beams of each sample are formed on chip (FP32) and interpolated as in
  * bf_form_tied_beams without leaving the compute unit.
  *
  *   volts     device uint8 [n_time][n_chan][n_pol][n_ns][n_ew] (full channel set)
@@ -204,8 +210,7 @@ size_t bf_tied_workspace_size(const bf_plan *plan, int32_t n_chan_sub, int64_t c
  * blocks; per chunk the complex FFT beams of the channel range are written to
  * the caller's workspace by the FFT beamformer (FP32, with the taper) and
  * interpolated from there by the bf_form_tied_beams kernels, both on
- * `stream`, so the method is the same as on the 4 x 16 lattice (interpolated
- * FFT beams) with the beams passing through HBM.  The chunk is the largest
+ * `stream`, the beams passing through HBM.  The chunk is the largest
  * whole number of blocks whose beams fit in workspace_bytes (at most n_time).
  * On the 4 x 16 lattice with block a multiple of 16 this is
  * bf_form_tied_beams_v and the workspace is not used (it may be NULL).
@@ -271,8 +276,8 @@ bf_status bf_accumulate_intensity(const void *z, int64_t n_time, int64_t n_serie
  * j < k, with their full-kernel weights; an approximation, much cheaper
  * than the dense form.
  *
- * The weights are generated in FP64 on the device at creation and stored in
- * FP32 (owned by the regrid object); the contraction runs in FP32.
+ * The weights are generated in FP64 on the device at creation and rounded to
+ * FP32 (owned by the regrid object); the contraction has FP32 operands and sums.
  */
 typedef struct bf_regrid bf_regrid;
 
@@ -338,15 +343,15 @@ bf_status bf_localize(const bf_plan *plan, const float *fft_intensity, int64_t n
  * ---- Tied-beam server --------------------------------------------------
  * Serves tied-array beam requests (arbitrary pointings, a contiguous channel
  * range, the most recent n_time samples) from a device-resident voltage ring
- * of the 4 x 16 lattice.  The beams are the interpolated FFT beams of
- * bf_form_tied_beams_v; pointed beams formed from FFT beams are the use the
+ * of the 4 x 16 lattice.  The beams are those of bf_form_tied_beams_v
+ * without a taper; pointed beams formed from FFT beams are the use the
  * paper gives for the regridding of eq. e:bp_max_arbitrary (Sec. "Discussion
  * and Conclusions": tied-array beams from FFT beams).
  *
  * Requests are admitted against a fixed device-memory budget (outputs and
  * pointing tables live in one pool of hbm_budget bytes), cut into tiles
  * (channel x up to 64 pointings x blocks_per_tile blocks of 16 samples; each
- * tile forms its FP64 interpolation weights once, so longer tiles amortise
+ * tile forms its FP64 weights once, so longer tiles amortise
  * them: 32 blocks served the benchmark's request mix with the lowest p99) and
  * batched -- round robin over the active requests, at most
  * max_tiles_per_launch tiles and two launches in flight -- into launches of

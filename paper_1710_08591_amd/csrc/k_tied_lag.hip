@@ -28,7 +28,7 @@
 // per 16 samples x 16 pointings).  Bound now by vector issue in the R_d of
 // each block; the voltages and outputs alone take 67 us at the copy rate.
 // The server's tiles: 24 requests of up to 256 pointings, 65536 samples and
-// 256 channels in one burst 7.58 -> 3.22 ms, 1.9 ms of it this kernel.
+// 256 channels in one burst 7.58 -> 2.38 ms, 2.0 ms of it this kernel.
 #include "dev_bytes.h"
 #include "dev_common.h"
 #include "kernels.h"
