@@ -122,8 +122,11 @@ __device__ __forceinline__ void ew_weighted(uint32_t d, const float* h, cf (&b)[
 // One wavefront per (block, channel, polarisation group).  Lane l = 16 g + n:
 // stage 1 holds a1 = 4 g + q (q < 4) and k2 = 16 kt + n (kt < 2); stage 2
 // takes E-W beam 2 p + (l >> 5) of pair p and k2 = l & 31.  The weights are
-// scaled by a power of two so that the largest lies in [1/2, 1) and the low
-// terms stay in FP16's normal range; the block sums are scaled back exactly.
+// scaled by a power of two so that the largest lies in [2^8, 2^9): an E-W sum
+// is below 64 of the largest, 2^15, within FP16, and the low terms of sums
+// down to 2^-12 of the largest weight keep their bits; the block sums are
+// scaled back exactly.  Scaled to [1/2, 1) the low terms of weights of e^{+-2}
+// were already subnormal.
 template <bool TAN, bool GAIN>
 __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per_eu(3))) void k_mix256(MixArgs a) {
   constexpr int N = 256, M = 512, HW = GAIN ? 8 : 4;
@@ -141,8 +144,8 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
   cf* const tile = reinterpret_cast<cf*>(lds_raw);
   const int n = lane & 15, g = lane >> 4;
 
-  // the weights, scaled by 2^-ex with 2^ex the power of two just above the
-  // largest component (every wavefront looks at them all)
+  // the weights, scaled by 2^-ex: the largest component in [2^8, 2^9) (every
+  // wavefront looks at them all)
   int ex;
   float hw[4][TAN ? 1 : HW];                  // at the lane's N-S positions n + 64 g + 16 i
   {
@@ -155,7 +158,7 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
     }
 #pragma unroll
     for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
-    ex = m > 0.f && m < INFINITY ? ilogbf(m) + 1 : 0;
+    ex = m > 0.f && m < INFINITY ? ilogbf(m) - 8 : 0;
     if constexpr (TAN) {
       for (int i = tid; i < N * HW; i += 64 * kWpg) lds_h[i] = ldexpf(a.taper[i], -ex);
       for (int i = tid; i < 32 * dit_slots(16); i += 64 * kWpg)

@@ -77,3 +77,23 @@ def test_zero_and_infinite_weights():
     assert not np.any(np.isfinite(_run(v, h, 16)))
     h[3, 1] = np.nan
     assert np.all(np.isnan(_run(v, h, 16)))
+
+
+@pytest.mark.parametrize("gains", [False, True])
+def test_strong_weight_of_a_dead_antenna(gains):
+    """The largest weight belongs to an antenna without data: the sums of the
+    others keep their bits.  Their errors are those of the same weights
+    without it, for which the 2-norm of |B|^2's relative error is about
+    1e-7 (two roundings of 2^-24 per value of each of the 9 + 3 stages, added
+    in squares: 2 * sqrt(12 / 3) * 2^-24 / sqrt(2) = 1.7e-7 at most)."""
+    rng = np.random.default_rng(6)
+    v = _volts(2, 1, 64, 12)
+    v[:, :, :, 7, 1] = 0
+    h = rng.uniform(0.2, 1.3, (256, 4))
+    if gains:
+        h = h * np.exp(1j * rng.uniform(-np.pi, np.pi, (256, 4)))
+    h[7, 1] = 1000.0
+    h = h.astype(np.complex64 if gains else np.float32)
+    got = _run(v, h, 16, gains=gains)
+    ref = orc.beamform_fft(v, 4, 512, 16, taper=h.astype(np.complex128 if gains else np.float64))
+    assert np.linalg.norm(got - ref) < 1.7e-7 * np.linalg.norm(ref)
