@@ -28,6 +28,13 @@
 // component, the factor Re W carried into stage 2 as the 25 multipliers of
 // column k2 (LDS, two wavefronts share them and the weights).  FP16 plans:
 // whole twiddles, the weights in registers; faster, less accurate.
+//
+// Where most weights lie more than 2^12 below the largest (a dead antenna with
+// a calibration of 1e6, say), the low terms of the others would be lost, so
+// each frame's sums are scaled by their own largest (wide_range): an error of
+// 2^-40 of it at most, below FP32's rounding.  930 us for the window below,
+// 1035 us for gains (967 and 1042 on the vector units, 800 and 900 without);
+// other weights pay 32 compares per wavefront for the rule, not measurable.
 // 4 x 256, 64 channels, 2 polarisations, 256 blocks of 16 samples, 2-norm
 // errors against 64 bits: FP32 window 1065 -> 860 us (1.05e-7 -> 1.02e-7; the
 // whole transform on the vector units before), FP16 window 832 -> 790 us
@@ -38,6 +45,8 @@
 #include "dev_common.h"
 #include "dev_f16.h"
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace fftbf {
 
@@ -119,6 +128,19 @@ __device__ __forceinline__ void ew_weighted(uint32_t d, const float* h, cf (&b)[
   b[3] = cf{m[0].r - m[1].i, m[0].i + m[1].r};
 }
 
+// Exponent that takes the largest of the wavefront's m >= 0 to [2^14, 2^15);
+// 0 for zero and infinity.  Positive floats are ordered as their bits are.
+__device__ __forceinline__ int frame_exponent(float m) {
+  int v = __float_as_int(m);
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true));   // row_ror 8, 4, 2, 1
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x122, 0xF, 0xF, true));
+  v = max(v, __builtin_amdgcn_mov_dpp(v, 0x121, 0xF, 0xF, true));
+  v = max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
+          max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
+  return v == 0 || v >= 0x7F800000 ? 0 : (v >> 23) - 127 - 14;
+}
+
 // One wavefront per (block, channel, polarisation group).  Lane l = 16 g + n:
 // stage 1 holds a1 = 4 g + q (q < 4) and k2 = 16 kt + n (kt < 2); stage 2
 // takes E-W beam 2 p + (l >> 5) of pair p and k2 = l & 31.  The weights are
@@ -147,19 +169,33 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
   // the weights, scaled by 2^-ex: the largest component in [2^8, 2^9) (every
   // wavefront looks at them all)
   int ex;
+  bool wide = false;
   float hw[4][TAN ? 1 : HW];                  // at the lane's N-S positions n + 64 g + 16 i
   {
-    float m = 0.f;
+    constexpr int PER = HW / 4;               // floats per weight
+    float m = 0.f, mag[16];                   // the larger component of the lane's 16 weights
     const float4* const h4 = reinterpret_cast<const float4*>(a.taper);
 #pragma unroll
     for (int i = 0; i < N * HW / 256; ++i) {
       const float4 v = h4[lane + 64 * i];
-      m = fmaxf(m, fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
+      const float f[4] = {fabsf(v.x), fabsf(v.y), fabsf(v.z), fabsf(v.w)};
+#pragma unroll
+      for (int k = 0; k < 4; k += PER) {
+        float& w = mag[(4 * i + k) / PER];
+        w = fmaxf(f[k], f[k + PER - 1]);
+        m = fmaxf(m, w);
+      }
     }
 #pragma unroll
     for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
     ex = m > 0.f && m < INFINITY ? ilogbf(m) - 8 : 0;
     if constexpr (TAN) {
+      // the rule: fewer than half of the weights other than zero within 2^-12 of the largest
+      const float low = ldexpf(m, -12);
+      int net = 0;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) net += 2 * __popcll(__ballot(mag[i] >= low)) - __popcll(__ballot(mag[i] > 0.f));
+      wide = m > 0.f && net < 0;
       for (int i = tid; i < N * HW; i += 64 * kWpg) lds_h[i] = ldexpf(a.taper[i], -ex);
       for (int i = tid; i < 32 * dit_slots(16); i += 64 * kWpg)
         lds_mu[i / dit_slots(16)][i % dit_slots(16)] = a.mult[i];
@@ -217,7 +253,7 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
   const int64_t frame_stride = (int64_t)a.n_chan * a.n_pol * N;   // dwords per sample
   const int64_t t0 = (int64_t)blk * a.block;
 
-  auto frame = [&](const uint32_t (&dw)[4]) {
+  auto frame = [&](auto wide_range, const uint32_t (&dw)[4]) {
     cf xw[4][4];                              // [E-W beam][position]
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -238,6 +274,17 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
       }
 #pragma unroll
       for (int e = 0; e < 4; ++e) xw[e][i] = b[e];
+    }
+    // wide_range: the frame's sums scaled by 2^-fex, the largest in [2^14, 2^15)
+    int fex = 0;
+    if constexpr (decltype(wide_range)::value) {
+      float m = 0.f;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) m = fmaxf(fmaxf(m, fabsf(xw[i >> 2][i & 3].r)), fabsf(xw[i >> 2][i & 3].i));
+      fex = frame_exponent(m);
+#pragma unroll
+      for (int i = 0; i < 16; ++i)
+        xw[i >> 2][i & 3] = cf{ldexpf(xw[i >> 2][i & 3].r, -fex), ldexpf(xw[i >> 2][i & 3].i, -fex)};
     }
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
@@ -264,7 +311,11 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
           cf z[4];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const float yr = y[kt][0][q], yi = y[kt][1][q];
+            float yr = y[kt][0][q], yi = y[kt][1][q];
+            if constexpr (decltype(wide_range)::value) {
+              yr = ldexpf(yr, fex);
+              yi = ldexpf(yi, fex);
+            }
             if constexpr (!TAN) z[q] = cmul(cf{yr, yi}, tw[kt][q]);
             else if (kt == 0) z[q] = cf{fmaf(-tt[0][q], yi, yr), fmaf(tt[0][q], yr, yi)};
             else z[q] = cf{fmaf(-tt[1][q], yi, pr[q] * yr), fmaf(tt[1][q], yr, pr[q] * yi)};
@@ -307,28 +358,32 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
     }
   };
 
-  for (int pol = pol_lo; pol < pol_hi; ++pol) {
-    // the lane's N-S positions a1 + 16 a2 = n + 64 g + 16 i, i < 4
-    const uint32_t* src = a.volts + ((int64_t)chan * a.n_pol + pol) * N + n + 64 * g;
-    const uint32_t* last = src + (t0 + a.block - 1) * frame_stride;
-    uint32_t b0[4], b1[4];
-    const uint32_t* q0 = src + t0 * frame_stride;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) b0[i] = __builtin_nontemporal_load(q0 + 16 * i);
-    // two frame buffers in turn; the load past the block's last frame
-    // re-reads that frame (cached), so no load is conditional
-    for (int s = 0; s < a.block; s += 2) {
-      const uint32_t* q1 = (s + 1 < a.block) ? q0 + frame_stride : last;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) b1[i] = __builtin_nontemporal_load(q1 + 16 * i);
-      frame(b0);
-      if (s + 1 >= a.block) break;
-      q0 = (s + 2 < a.block) ? q1 + frame_stride : last;
+  auto run = [&](auto wide_range) {
+    for (int pol = pol_lo; pol < pol_hi; ++pol) {
+      // the lane's N-S positions a1 + 16 a2 = n + 64 g + 16 i, i < 4
+      const uint32_t* src = a.volts + ((int64_t)chan * a.n_pol + pol) * N + n + 64 * g;
+      const uint32_t* last = src + (t0 + a.block - 1) * frame_stride;
+      uint32_t b0[4], b1[4];
+      const uint32_t* q0 = src + t0 * frame_stride;
 #pragma unroll
       for (int i = 0; i < 4; ++i) b0[i] = __builtin_nontemporal_load(q0 + 16 * i);
-      frame(b1);
+      // two frame buffers in turn; the load past the block's last frame
+      // re-reads that frame (cached), so no load is conditional
+      for (int s = 0; s < a.block; s += 2) {
+        const uint32_t* q1 = (s + 1 < a.block) ? q0 + frame_stride : last;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b1[i] = __builtin_nontemporal_load(q1 + 16 * i);
+        frame(wide_range, b0);
+        if (s + 1 >= a.block) break;
+        q0 = (s + 2 < a.block) ? q1 + frame_stride : last;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) b0[i] = __builtin_nontemporal_load(q0 + 16 * i);
+        frame(wide_range, b1);
+      }
     }
-  }
+  };
+  if (TAN && wide) run(std::true_type{});
+  else run(std::false_type{});
 
   // ---- block end: beams A = k2 + 32 k1 of E-W beam 2p + es, clamp, store ----
   float* lds_i = reinterpret_cast<float*>(lds_raw);

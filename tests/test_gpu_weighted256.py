@@ -80,9 +80,11 @@ def test_zero_and_infinite_weights():
 
 
 @pytest.mark.parametrize("gains", [False, True])
-def test_strong_weight_of_a_dead_antenna(gains):
+@pytest.mark.parametrize("strong", [1000.0, 3000.0, 1e6, 1e20])
+def test_strong_weight_of_a_dead_antenna(gains, strong):
     """The largest weight belongs to an antenna without data: the sums of the
-    others keep their bits.  Their errors are those of the same weights
+    others keep their bits, on either side of the 2^12 below the largest
+    weight from which on each frame is scaled by itself.  Their errors are those of the same weights
     without it, for which the 2-norm of |B|^2's relative error is about
     1e-7 (two roundings of 2^-24 per value of each of the 9 + 3 stages, added
     in squares: 2 * sqrt(12 / 3) * 2^-24 / sqrt(2) = 1.7e-7 at most)."""
@@ -92,8 +94,27 @@ def test_strong_weight_of_a_dead_antenna(gains):
     h = rng.uniform(0.2, 1.3, (256, 4))
     if gains:
         h = h * np.exp(1j * rng.uniform(-np.pi, np.pi, (256, 4)))
-    h[7, 1] = 1000.0
+    h[7, 1] = strong
     h = h.astype(np.complex64 if gains else np.float32)
     got = _run(v, h, 16, gains=gains)
     ref = orc.beamform_fft(v, 4, 512, 16, taper=h.astype(np.complex128 if gains else np.float64))
     assert np.linalg.norm(got - ref) < 1.7e-7 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("gains", [False, True])
+@pytest.mark.parametrize("spread", [3.0, 9.0])
+def test_wide_range_of_weights(gains, spread):
+    """Weights over several decades, with zeros among them and a block whose
+    samples are all zero (frames without a largest value)."""
+    rng = np.random.default_rng(8)
+    v = _volts(2, 2, 48, 13)
+    v[16:32, 0] = 0
+    h = np.exp(spread * rng.normal(size=(256, 4))) * (rng.random((256, 4)) < 0.8)
+    if gains:
+        h = h * np.exp(1j * rng.uniform(-np.pi, np.pi, (256, 4)))
+    h = h.astype(np.complex64 if gains else np.float32)
+    got = _run(v, h, 16, gains=gains)
+    ref = orc.beamform_fft(v, 4, 512, 16, taper=h.astype(np.complex128 if gains else np.float64))
+    assert not np.any(got[1, 0])
+    live = ref > 0
+    assert rel_err(got[live], ref[live]) < TOL_FP32
