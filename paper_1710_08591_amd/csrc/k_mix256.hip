@@ -32,7 +32,7 @@
 // Where most weights lie more than 2^12 below the largest (a dead antenna with
 // a calibration of 1e6, say), the low terms of the others would be lost, so
 // each frame's sums are scaled by their own largest (wide_range): an error of
-// 2^-40 of it at most, below FP32's rounding.  930 us for the window below,
+// 2^-39 of it at most, below FP32's rounding.  930 us for the window below,
 // 1035 us for gains (967 and 1042 on the vector units, 800 and 900 without);
 // other weights pay 32 compares per wavefront for the rule, not measurable.
 // 4 x 256, 64 channels, 2 polarisations, 256 blocks of 16 samples, 2-norm
