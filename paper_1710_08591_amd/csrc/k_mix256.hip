@@ -13,8 +13,11 @@
 //   C[a1][k2] = A[a1][(a2, re|im)] * B[(a2, re|im)][k2]
 // A holds the weighted E-W sums of the E-W beam at N-S position a1 + 16 a2 and
 // B the realified coefficients, each as two FP16 terms (hi + lo, about 22
-// significant bits); three products, the smallest first, accumulate into the
-// same FP32 accumulators, so stage 1 is accurate to FP32 rounding.
+// significant bits); three products accumulate into the same FP32
+// accumulators, so stage 1 is accurate to FP32 rounding.  FP32 plans take the
+// smallest first; FP16 plans the largest, which needs no low terms yet: a
+// lone wavefront per SIMD (4 x 256, 11 channels, 13 blocks of 80 samples)
+// takes 151 us that way and 158 the other, which gains 2 % on a full chip.
 //
 // Stage 2 is the FP32 16-point DFT over a1 in registers, one (E-W beam, k2)
 // per lane.  The data go from the stage-1 layout (lane = (a1 group, k2)) to
@@ -37,8 +40,8 @@
 // other weights pay 32 compares per wavefront for the rule, not measurable.
 // 4 x 256, 64 channels, 2 polarisations, 256 blocks of 16 samples, 2-norm
 // errors against 64 bits: FP32 window 1065 -> 860 us (1.05e-7 -> 1.02e-7; the
-// whole transform on the vector units before), FP16 window 832 -> 790 us
-// (1.14e-7 -> 1.10e-7).  Bound by vector issue: about 750 instructions per
+// whole transform on the vector units before), FP16 window 832 us (1.12e-7).
+// Bound by vector issue: about 750 instructions per
 // frame and wavefront, 48 matrix products behind them (a fourth product each
 // costs nothing).  Both stages on the matrix cores, without the LDS tile, took
 // 893 us: splitting Z costs what the DFT's instructions do.
@@ -301,10 +304,11 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
         for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
           for (int part = 0; part < 2; ++part) {
-            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Al, B1[0][kt][part], f32x4{0.f, 0.f, 0.f, 0.f},
+            const half8 A0 = TAN ? Al : Ah, A2 = TAN ? Ah : Al;
+            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A0, B1[0][kt][part], f32x4{0.f, 0.f, 0.f, 0.f},
                                                                  0, 0, 0);
             y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, B1[1][kt][part], y[kt][part], 0, 0, 0);
-            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(Ah, B1[0][kt][part], y[kt][part], 0, 0, 0);
+            y[kt][part] = __builtin_amdgcn_mfma_f32_16x16x32_f16(A2, B1[0][kt][part], y[kt][part], 0, 0, 0);
           }
 #pragma unroll
         for (int kt = 0; kt < 2; ++kt) {
