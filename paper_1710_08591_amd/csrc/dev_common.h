@@ -381,12 +381,9 @@ __device__ __forceinline__ int pol_pair_task(int w, int n_wg, int n_pg, int& pg)
   return w / n_pg;
 }
 
-// Signed 4-bit dot product of the eight nibbles of a and b, accumulator 0
-// (the three-operand VOP3P form, so no register has to be zeroed first).
-__device__ __forceinline__ int sdot8(int a, int b) {
-  int r;
-  asm("v_dot8_i32_i4 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
+// Signed 4-bit dot product of the eight nibbles of a and b, added to c.  With
+// the clamp (which int32 sums of 512 at most never reach) the compiler takes
+// the three-operand form, so a constant c needs no register of its own.
+__device__ __forceinline__ int sdot8(int a, int b, int c = 0) { return __builtin_amdgcn_sdot8(a, b, c, true); }
 
 }  // namespace fftbf

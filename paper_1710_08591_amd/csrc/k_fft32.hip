@@ -339,8 +339,8 @@ __attribute__((amdgpu_waves_per_eu(fft32_min_waves<N, G, TAPER, CPLX, FOLD>())))
             int sr = 0, si = 0;
 #pragma unroll
             for (int f = 0; f < FOLD; ++f) {
-              sr += sdot8((int)cur[j + L * f], wre);
-              si += sdot8((int)cur[j + L * f], wim);
+              sr = sdot8((int)cur[j + L * f], wre, sr);
+              si = sdot8((int)cur[j + L * f], wim, si);
             }
             x[j] = cf{(float)sr, (float)si};
           } else if constexpr (TAPER == 3) {

@@ -91,8 +91,8 @@ __device__ __forceinline__ half8 ew_sums_f16(const uint32_t* dw, int w) {
   half8 A;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t lo = (uint32_t)sdot8_acc((int)dw[2 * j], w, 0x6600);
-    const uint32_t hi = (uint32_t)sdot8_acc((int)dw[2 * j + 1], w, 0x6600);
+    const uint32_t lo = (uint32_t)sdot8((int)dw[2 * j], w, 0x6600);
+    const uint32_t hi = (uint32_t)sdot8((int)dw[2 * j + 1], w, 0x6600);
     const half2 v = __builtin_bit_cast(half2, __builtin_amdgcn_perm(hi, lo, 0x05040100u)) -
                     half2{(_Float16)1536.0f, (_Float16)1536.0f};
     A[2 * j] = v[0];
