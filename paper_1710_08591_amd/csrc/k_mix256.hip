@@ -38,15 +38,15 @@
 // FP16 plans: whole twiddles, the weights in registers, two roundings; faster,
 // less accurate.
 //
-// Where most weights lie more than 2^12 below the largest (a dead antenna with
-// a calibration of 1e6, say), the low terms of the others would be lost, so
-// each frame's sums are scaled by their own largest (wide_range): an error of
-// 2^-39 of it at most, below FP32's rounding.  930 us for the window below,
-// 1035 us for gains (967 and 1042 on the vector units, 800 and 900 without);
-// other weights pay 32 compares per wavefront for the rule, not measurable.
-// 4 x 256, 64 channels, 2 polarisations, 256 blocks of 16 samples, 2-norm
-// errors against 64 bits: FP32 window 1065 -> 860 us (1.05e-7 -> 1.02e-7; the
-// whole transform on the vector units before), FP16 window 832 us (1.12e-7).
+// Where any weight other than zero lies more than 2^10 below the largest, the
+// low terms of its sums would be lost.  That matters when the antennas of the
+// large weights hold no data (calibrations of 1e6 on two dead E-W columns,
+// say), so such weights are not scaled to the largest and each frame's sums are
+// scaled by their own largest instead (wide_range): an error of 2^-39 of it at most, below
+// FP32's rounding, over FP32's whole range.
+// 4 x 256, 64 channels, 2 polarisations, 128 blocks of 16 samples, whole
+// transform on the vector units -> this: window 488 -> 442 us (464 with a
+// frame scale), gains 519 -> 488 us (506 with a frame scale).
 // Bound by vector issue: about 750 instructions per
 // frame and wavefront, 48 matrix products behind them (a fourth product each
 // costs nothing).  Both stages on the matrix cores, without the LDS tile, took
@@ -154,10 +154,11 @@ __device__ __forceinline__ int frame_exponent(float m) {
 // stage 1 holds a1 = 4 g + q (q < 4) and k2 = 16 kt + n (kt < 2); stage 2
 // takes E-W beam 2 p + (l >> 5) of pair p and k2 = l & 31.  The weights are
 // scaled by a power of two so that the largest lies in [2^8, 2^9): an E-W sum
-// is below 64 of the largest, 2^15, within FP16, and the low terms of sums
-// down to 2^-12 of the largest weight keep their bits; the block sums are
-// scaled back exactly.  Scaled to [1/2, 1) the low terms of weights of e^{+-2}
-// were already subnormal.
+// is below 64 of the largest, 2^15, within FP16.  The terms of a sum then hold
+// it to 2^-25 (half of FP16's smallest step): 2^-23 of the product of the
+// smallest weight that the rule lets pass, 2^-2, with a voltage of 1.  The
+// block sums are scaled back exactly.  Scaled to [1/2, 1) the low terms of
+// weights of e^{+-2} were already subnormal.
 template <bool TAN, bool GAIN>
 __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per_eu(3))) void k_mix256(MixArgs a) {
   constexpr int N = 256, M = 512, HW = GAIN ? 8 : 4;
@@ -199,12 +200,14 @@ __global__ __launch_bounds__(64 * (TAN ? 2 : 1)) __attribute__((amdgpu_waves_per
     for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
     ex = m > 0.f && m < INFINITY ? ilogbf(m) - 8 : 0;
     if constexpr (TAN) {
-      // the rule: fewer than half of the weights other than zero within 2^-12 of the largest
-      const float low = ldexpf(m, -12);
-      int net = 0;
+      // the rule: a weight other than zero below 2^-10 of the largest
+      const float low = ldexpf(m, -10);
+      bool below = false;
 #pragma unroll
-      for (int i = 0; i < 16; ++i) net += 2 * __popcll(__ballot(mag[i] >= low)) - __popcll(__ballot(mag[i] > 0.f));
-      wide = m > 0.f && net < 0;
+      for (int i = 0; i < 16; ++i) below |= mag[i] > 0.f && mag[i] < low;
+      wide = __any(below);
+      // (strong weights: 2^-12 keeps a block sum of up to 1024 times the largest output finite)
+      if (wide) ex = m > 0x1p30f ? 6 : 0;
       for (int i = tid; i < N * HW; i += 64 * kWpg) lds_h[i] = ldexpf(a.taper[i], -ex);
       for (int i = tid; i < 32 * dit_slots(16); i += 64 * kWpg)
         lds_mu[i / dit_slots(16)][i % dit_slots(16)] = a.mult[i];
