@@ -374,18 +374,45 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     asm volatile("" : "+v"(fl_lane));      // the addresses below are formed here, not held through the loops
     const int ps = fl_lane / PL, l = fl_lane % PL;
     cd z[8];
+    // Rounding leaks about 2^-53 of one task's sums into the other's.  So that
+    // it stays that small beside the other's own, tasks whose R_0 differ by
+    // more than 2^8 are brought to the same size first (exactly, by 2^sh); a
+    // task without signal (R_0 = 0) is zero, its rounding noise is not stored.
+    float norm1, norm2;
     {
+      const sum_t p1 = own[ps * N], p2 = own[512 + ps * N];
+      sum_t ur[8], ui[8], vr[8], vi[8];
       const sum_t* const up = own + ps * N + l;
       const sum_t* const down = own + ps * N - l;
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const sum_t* const r = i < 4 ? up + PL * i : down + PL * (8 - i);
-        const sum_t ur = r[0], ui = r[256], vr = r[512], vi = r[768];
-        sum_t zr = i < 4 ? ur - vi : ur + vi;
-        sum_t zi = i < 4 ? ui + vr : vr - ui;
-        if (i == 4 && l == 0) zr = zi = 0;               // lag N: not formed
-        z[i] = cd{(double)zr, (double)zi};
+        ur[i] = r[0];
+        ui[i] = r[256];
+        vr[i] = r[512];
+        vi[i] = r[768];
       }
+      int sh = 0;
+      if (p1 != 0 && p2 != 0) sh = __builtin_amdgcn_frexp_exp((double)p1) - __builtin_amdgcn_frexp_exp((double)p2);
+      if (sh >= -8 && sh <= 8) sh = 0;
+      norm1 = p1 != 0 ? p.norm : 0.f;
+      norm2 = p2 != 0 ? ldexpf(p.norm, -sh) : 0.f;
+      if constexpr (PL == 64) {
+        norm1 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, norm1)));
+        norm2 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, norm2)));
+      }
+      if (!__any(sh != 0)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          z[i] = i < 4 ? cd{(double)(ur[i] - vi[i]), (double)(ui[i] + vr[i])} : cd{(double)(ur[i] + vi[i]), (double)(vr[i] - ui[i])};
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const double a = (double)ur[i], b = (double)ui[i], c = ldexp((double)vr[i], sh), d = ldexp((double)vi[i], sh);
+          z[i] = i < 4 ? cd{a - d, b + c} : cd{a + d, c - b};
+        }
+      }
+      if (l == 0) z[4] = cd{0.0, 0.0};                   // lag N: not formed
     }
     wave_sync();
     double2* const ex = reinterpret_cast<double2*>(plane);
@@ -442,8 +469,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     }
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      v1[k] = fmaxf((float)z[k].r * p.norm, 0.f);
-      v2[k] = fmaxf((float)z[k].i * p.norm, 0.f);
+      v1[k] = fmaxf((float)z[k].r * norm1, 0.f);
+      v2[k] = fmaxf((float)z[k].i * norm2, 0.f);
     }
     // value i of the lane: N-S beam beam(i) of this lane's series
     auto beam = [&](int i) {
