@@ -41,7 +41,7 @@ constexpr int kLagChunk = 32;              // blocks of one R_d table in LDS
 constexpr int kLagPitch = 272;             // bytes of one block's digits: 256, and 16 against bank conflicts
 constexpr int kLagPlane = 576;             // bytes of one E-W antenna's operands: 512, a zero entry, pad
 constexpr int kLagScratch = 4 * kLagPlane + 7 * 4 * 16 * 8;   // per wavefront: operands, then the R_d of its lane groups
-constexpr int kLagLds = 4 * kLagScratch + 3 * kLagChunk * kLagPitch;
+constexpr int kLagLds = 4 * kLagScratch + 3 * kLagChunk * kLagPitch + 64 * 4;
 // samples (times polarisations summed) whose R_d, at most 64 * 128 per
 // sample, fit three signed digits; longer blocks go in segments
 constexpr int kLagSegment = 512;
@@ -117,15 +117,20 @@ __device__ __forceinline__ void lag_weights(double y_ew, double y_ns, int g, v4i
 template <class Locate, class Store>
 __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int n_sum, double y_ew, double y_ns,
                                               bool wave_live, int64_t frame_dw, Locate group, Store store) {
-  const int lane = threadIdx.x & 63;
+  int lane = threadIdx.x & 63;
+  asm volatile("" : "+v"(lane));       // the addresses are formed here, not held (spilled) from tile to tile
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   char* const xs = lds + wave * kLagScratch;
   int2* const part = reinterpret_cast<int2*>(xs + 4 * kLagPlane);
   char* const rd = lds + 4 * kLagScratch;
+  float* const undefined = reinterpret_cast<float*>(rd + 3 * kLagChunk * kLagPitch) + 16 * wave;   // added to the outputs
   const int ln = lane & 15, grp = lane >> 4;
 
   v4i w[4][4];
   if (wave_live) lag_weights(y_ew, y_ns, grp, w);
+  // the weights' digits hold no NaN: a direction that is not finite makes the
+  // sums of its pointing mean nothing, and they are stored as NaN
+  if (grp == 0) undefined[ln] = fabs(y_ew) < INFINITY && fabs(y_ns) < INFINITY ? 0.f : NAN;
   if (lane < 4) *reinterpret_cast<v4i*>(xs + lane * kLagPlane + 512) = v4i{0, 0, 0, 0};
 
   // Operands of 16 samples: [E-W antenna][th][N-S antenna] 16 bytes, samples
@@ -269,12 +274,13 @@ __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int
     }
     if (wave_live) {
       constexpr double kScale = 1.0 / (536870912.0 * 64.0);     // weight step, 1/n
+      const float add = undefined[ln];
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int b = 16 * rt + 4 * grp + r;
-          if (b < nb) store(c0 + b, fmaxf((float)(out[rt][r] * kScale), 0.f));
+          if (b < nb) store(c0 + b, fmaxf((float)(out[rt][r] * kScale), 0.f) + add);
         }
     }
   }
