@@ -182,7 +182,9 @@ bf_status bf_form_tied_beams(const bf_plan *plan, const void *fft_beams, int64_t
 /*
  * Tied-array beams straight from voltages.  Without a taper the intensity of
  * each pointing is a sum over the block's stacked visibilities on both axes
- * (exact integers), with weights generated in FP64; with a taper the FFT
+ * (exact integers), with weights generated in FP64 and held to 2^-29, or to
+ * 2^-60 for outputs below 2^-13 of the antennas' summed power (a weak beam
+ * beside a strong source without noise); with a taper the FFT
  * beams of each sample are formed on chip (FP32) and interpolated as in
  * bf_form_tied_beams without leaving the compute unit.
  *

@@ -16,19 +16,20 @@
 // rounding: R_d in three signed base-256 digits, the weights (FP64, rounded
 // to a step of 2^-29) in four, products by digit pair summed in int32 and
 // joined in FP64.  A weak beam beside a strong source is a small difference
-// of large terms, which FP32 sums would lose.  (FP64 matrix products measured
+// of large terms, which FP32 sums would lose; the weakest take a second set of
+// weight digits, to 2^-60 (see kWeak).  (FP64 matrix products measured
 // 112 cycles per 16 x 16 x 4, seven times the digit products' time.)
 //
 // Work of one 32-block table on a SIMD: eight blocks' R_d, each 16 matrix
 // products and about 150 other vector instructions, once per wavefront its 16
 // pointings' weights (640 instructions, FP64), and per 16 blocks x 16
 // pointings 48 matrix products; three wavefronts per SIMD.  MI355X, 64
-// pointings, 256 channels, 16384 samples: 818 -> 159 us against interpolating
+// pointings, 256 channels, 16384 samples: 818 -> 162 us against interpolating
 // FFT beams per sample on the FP16 matrix cores (bound by those: 48 products
 // per 16 samples x 16 pointings).  Bound now by vector issue in the R_d of
 // each block; the voltages and outputs alone take 67 us at the copy rate.
 // The server's tiles: 24 requests of up to 256 pointings, 65536 samples and
-// 256 channels in one burst 7.58 -> 2.38 ms, 2.0 ms of it this kernel.
+// 256 channels in one burst 7.58 -> 2.10 ms.
 #include "dev_bytes.h"
 #include "dev_common.h"
 #include "kernels.h"
@@ -61,10 +62,23 @@ struct Group {
   int64_t back;
 };
 
+// The weights' step leaves an absolute error of up to 1e-10 of R_0 (a coherent
+// source's peak), 3e-11 in the mean.  Where a tile has outputs below 2^-13 of
+// their R_0, these are formed again with a second set of digits that holds what
+// the step left out: 1e-16 of R_0.  Noise beside a source that fills the voltages stays above
+// 2^-12.1 (25 million outputs of blocks of 16 samples), so data with noise do
+// not pay for it beyond the comparison (64 pointings, 256 channels, 16384 samples
+// 159 -> 162 us); without noise the same call takes 496 us (818 by FFT beams per
+// sample).
+constexpr float kWeak = 0x1p-13f;
+constexpr double kLowUnit = 2147483648.0;  // 2^31
+
 // Weight digits of one pointing (lane column p = l % 16, lane group g = l / 16):
 // byte 64 c + 16 g + 4 i + j of the K axis is, of the lag kappa = 16 c + 4 g + i
 // (dx = c - 3, dy = 4 g + i) and of kappa + 64 (dx = c + 1), the real part
-// (j = 0, 2) or the imaginary part (j = 1, 3).
+// (j = 0, 2) or the imaginary part (j = 1, 3).  LOW: what rounding to a step of
+// 2^-29 leaves of the weights, to a step of 2^-60.
+template <bool LOW>
 __device__ __forceinline__ void lag_weights(double y_ew, double y_ns, int g, v4i (&w)[4][4]) {
   cplx zx[4], ay[4];
   zx[0] = {1.0, 0.0};
@@ -82,7 +96,9 @@ __device__ __forceinline__ void lag_weights(double y_ew, double y_ns, int g, v4i
 
   constexpr double kUnit = 536870912.0, kRound = 6755399441055744.0;   // 2^29; 1.5 * 2^52: the sum's low word is the integer
   auto digits = [&](double v, double f) {
-    return signed_digits((int)(uint32_t)__builtin_bit_cast(uint64_t, fma(v, f * kUnit, kRound)));
+    double u = fma(v, f * kUnit, kRound);
+    if constexpr (LOW) u = fma(fma(v, f * kUnit, kRound - u), kLowUnit, kRound);
+    return signed_digits((int)(uint32_t)__builtin_bit_cast(uint64_t, u));
   };
 #pragma unroll
   for (int c = 0; c < 4; ++c)
@@ -113,13 +129,12 @@ __device__ __forceinline__ void lag_weights(double y_ew, double y_ns, int g, v4i
 // Intensities of up to 64 pointings (16 per wavefront) over n_blk blocks of
 // 16 gpb samples, n_sum polarisations summed.  group(s, k): where the 16
 // samples from sample s on (of the first block's start), polarisation k, lie.
-// store(block, value) of this lane's pointing.
-template <class Locate, class Store>
-__device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int n_sum, double y_ew, double y_ns,
-                                              bool wave_live, int64_t frame_dw, Locate group, Store store) {
-  int lane = threadIdx.x & 63;
-  asm volatile("" : "+v"(lane));       // the addresses are formed here, not held (spilled) from tile to tile
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+// store(block, value) of this lane's pointing.  Returns whether any output is
+// so weak that it needs the weights' low digits; FULL forms and stores those
+// outputs, and no others (so none depends on its neighbours).
+template <bool FULL, class Locate, class Store>
+__device__ __forceinline__ bool tied_lag_pass(char* lds, int lane, int wave, int n_blk, int gpb, int n_sum, double y_ew,
+                                              double y_ns, bool wave_live, int64_t frame_dw, Locate group, Store store) {
   char* const xs = lds + wave * kLagScratch;
   int2* const part = reinterpret_cast<int2*>(xs + 4 * kLagPlane);
   char* const rd = lds + 4 * kLagScratch;
@@ -127,7 +142,8 @@ __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int
   const int ln = lane & 15, grp = lane >> 4;
 
   v4i w[4][4];
-  if (wave_live) lag_weights(y_ew, y_ns, grp, w);
+  if (!FULL && wave_live) lag_weights<false>(y_ew, y_ns, grp, w);
+  bool weak = false;
   // the weights' digits hold no NaN: a direction that is not finite makes the
   // sums of its pointing mean nothing, and they are stored as NaN
   if (grp == 0) undefined[ln] = fabs(y_ew) < INFINITY && fabs(y_ns) < INFINITY ? 0.f : NAN;
@@ -154,11 +170,12 @@ __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int
   for (int j = 0; j < 4; ++j) off[j] = (4 * grp + j) * frame_dw + ln;
   for (int c0 = 0; c0 < n_blk; c0 += kLagChunk) {
     const int nb = n_blk - c0 < kLagChunk ? n_blk - c0 : kLagChunk;
-    double out[2][4];
+    float limit = 0.f;                     // 2^-13 R_0 of the table's block lane % 32
+    double out[2][4], rest[2][4];
 #pragma unroll
     for (int rt = 0; rt < 2; ++rt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) out[rt][r] = 0.0;
+      for (int r = 0; r < 4; ++r) out[rt][r] = rest[rt][r] = 0.0;
     for (int g0 = 0; g0 < gpb; g0 += seg) {
       const int ng = gpb - g0 < seg ? gpb - g0 : seg;
       const int n_item = ng * n_sum;
@@ -246,7 +263,7 @@ __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int
       __syncthreads();
 
       // ---- contraction with the weights: 16 blocks x 16 pointings ----
-      if (wave_live) {
+      auto contract = [&](double (&sum)[2][4]) {
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
           if (16 * rt >= nb) break;
@@ -266,8 +283,24 @@ __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int
             double t = (double)s[5][r];
 #pragma unroll
             for (int k = 4; k >= 0; --k) t = fma(t, 256.0, (double)s[k][r]);
-            out[rt][r] += t;
+            sum[rt][r] += t;
           }
+        }
+      };
+      if (wave_live) {
+        const int8_t* const r0 = reinterpret_cast<const int8_t*>(rd) + (lane % kLagChunk) * kLagPitch + 4 * 48;
+        constexpr int kPlane = kLagChunk * kLagPitch;
+        limit = fmaf(kWeak, (float)(65536 * r0[2 * kPlane] + 256 * r0[kPlane] + r0[0]), limit);
+        if (lane < kLagChunk) reinterpret_cast<float*>(xs)[lane] = limit;
+        if constexpr (FULL) {
+          asm volatile("" : "+v"(y_ew), "+v"(y_ns));     // made again here: what the two sets share is not held
+          lag_weights<false>(y_ew, y_ns, grp, w);
+        }
+        contract(out);
+        if constexpr (FULL) {
+          asm volatile("" : "+v"(y_ew), "+v"(y_ns));
+          lag_weights<true>(y_ew, y_ns, grp, w);
+          contract(rest);
         }
       }
       __syncthreads();               // the R_d table may be overwritten
@@ -275,34 +308,49 @@ __device__ __forceinline__ void tied_lag_tile(char* lds, int n_blk, int gpb, int
     if (wave_live) {
       constexpr double kScale = 1.0 / (536870912.0 * 64.0);     // weight step, 1/n
       const float add = undefined[ln];
+      float4 low[2];
 #pragma unroll
-      for (int rt = 0; rt < 2; ++rt)
+      for (int rt = 0; rt < 2; ++rt) low[rt] = reinterpret_cast<const float4*>(xs)[4 * rt + grp];
+#pragma unroll
+      for (int rt = 0; rt < 2; ++rt) {
+        const float lim[4] = {low[rt].x, low[rt].y, low[rt].z, low[rt].w};
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int b = 16 * rt + 4 * grp + r;
-          if (b < nb) store(c0 + b, fmaxf((float)(out[rt][r] * kScale), 0.f) + add);
+          const float v = fmaxf((float)(out[rt][r] * kScale), 0.f);
+          const bool low_one = b < nb && v < lim[r];
+          if constexpr (FULL) {
+            if (low_one) store(c0 + b, fmaxf((float)(fma(rest[rt][r], 1.0 / kLowUnit, out[rt][r]) * kScale), 0.f) + add);
+          } else {
+            weak |= low_one;
+            if (b < nb) store(c0 + b, v + add);
+          }
         }
+      }
     }
   }
+  return weak;
 }
 
 // One workgroup per (64 pointings, run of blocks, channel, polarisation group).
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_tied_lag(TiedArgs a) {
-  __shared__ __attribute__((aligned(16))) char lds[kLagLds];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+template <bool FULL>
+__device__ __forceinline__ bool tied_lag_run(const TiedArgs& a, char* lds) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));        // nothing of one pass is held (spilled) for the other
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_ptile = (a.n_point + 63) / 64;
   const int n_pg = a.pol_sum ? 1 : a.n_pol;
   const int ptile = blockIdx.x % n_ptile, run = blockIdx.x / n_ptile;
   const int cs = blockIdx.y, pg = blockIdx.z, chan = a.chan_lo + cs;
-  const int p0 = ptile * 64 + wave * 16, p = p0 + (lane & 15);
+  const int p0 = ptile * 64 + wave * 16, p = p0 + (tid & 15);
   const int pp = p < a.n_point ? p : a.n_point - 1;
   const int64_t n_blk = a.n_time / a.block, b0 = (int64_t)run * a.run_units;
   const int nb = (int)(n_blk - b0 < a.run_units ? n_blk - b0 : a.run_units);
   const int64_t frame_dw = (int64_t)a.n_chan * a.n_pol * 16;
   const uint32_t* const src = a.volts + b0 * a.block * frame_dw + ((int64_t)chan * a.n_pol + pg) * 16;
   float* const out = static_cast<float*>(a.out);
-  tied_lag_tile(
-      lds, nb, a.block / 16, a.pol_sum ? a.n_pol : 1, a.dl[2 * chan] * a.dircos[2 * pp],
+  return tied_lag_pass<FULL>(
+      lds, tid & 63, wave, nb, a.block / 16, a.pol_sum ? a.n_pol : 1, a.dl[2 * chan] * a.dircos[2 * pp],
       a.dl[2 * chan + 1] * a.dircos[2 * pp + 1], p0 < a.n_point, frame_dw,
       [&](int64_t s, int k) { return Group{src + s * frame_dw + k * 16, 16, 0}; },
       [&](int b, float v) {
@@ -310,39 +358,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
       });
 }
 
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_tied_lag(TiedArgs a) {
+  __shared__ __attribute__((aligned(16))) char lds[kLagLds];
+  if (__builtin_expect(__syncthreads_or(tied_lag_run<false>(a, lds)), 0)) tied_lag_run<true>(a, lds);
+}
+
+// One polarisation of a server's tile (request, channel, 64 pointings, run of
+// 16-sample blocks), from the device ring (absolute sample s lives in slot
+// s mod ring_samples).
+template <bool FULL>
+__device__ __forceinline__ bool serve_run(char* lds, const ServeTile* __restrict__ tile, const uint32_t* __restrict__ ring,
+                                          int64_t ring_samples, int n_chan, int n_pol, int pol,
+                                          const double* __restrict__ dl) {
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));        // nothing is held (spilled) from tile to tile, or of one pass for the other
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t frame_dw = (int64_t)n_chan * n_pol * 16;
+  const ServeTile t = *tile;
+  const int p0 = t.ptile * 64 + wave * 16, p = p0 + (tid & 15);
+  const int pp = p < t.n_point ? p : t.n_point - 1;
+  const int64_t first = (t.t_start + (int64_t)t.blk0 * 16) % ring_samples;   // a window is at most the ring
+  const uint32_t* const src = ring + ((int64_t)t.chan * n_pol + pol) * 16;
+  return tied_lag_pass<FULL>(
+      lds, tid & 63, wave, t.n_blk, 1, 1, dl[2 * t.chan] * t.dircos[2 * pp], dl[2 * t.chan + 1] * t.dircos[2 * pp + 1],
+      p0 < t.n_point, frame_dw,
+      [&](int64_t s, int) {
+        int64_t slot = first + s;
+        if (slot >= ring_samples) slot -= ring_samples;
+        const int64_t left = ring_samples - slot;
+        return Group{src + slot * frame_dw, left < 16 ? (int)left : 16, ring_samples * frame_dw};
+      },
+      [&](int b, float v) {
+        if (p < t.n_point)
+          t.out[(((int64_t)(t.blk0 + b) * t.n_chan_req + (t.chan - t.chan_lo)) * n_pol + pol) * t.n_point + p] = v;
+      });
+}
+
 // Persistent tile worker of the tied-beam server: each workgroup takes tiles
-// (request, channel, 64 pointings, run of 16-sample blocks) from the batch,
-// reading voltages from the device ring (absolute sample s lives in slot
-// s mod ring_samples).  A tile's arithmetic is exact up to its last
-// rounding and does not depend on which other tiles share the launch.
+// from the batch.  A tile's arithmetic is exact up to its last rounding and does
+// not depend on which other tiles share the launch.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_serve(const ServeTile* __restrict__ tiles, int n_tiles,
                                                const uint32_t* __restrict__ ring, int64_t ring_samples,
                                                int n_chan, int n_pol, const double* __restrict__ dl) {
   __shared__ __attribute__((aligned(16))) char lds[kLagLds];
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-  const int64_t frame_dw = (int64_t)n_chan * n_pol * 16;
-  for (int ti = blockIdx.x; ti < n_tiles; ti += gridDim.x) {
-    const ServeTile t = tiles[ti];
-    const int p0 = t.ptile * 64 + wave * 16, p = p0 + (lane & 15);
-    const int pp = p < t.n_point ? p : t.n_point - 1;
-    const int64_t first = (t.t_start + (int64_t)t.blk0 * 16) % ring_samples;   // a window is at most the ring
+  for (int ti = blockIdx.x; ti < n_tiles; ti += gridDim.x)
     for (int pol = 0; pol < n_pol; ++pol) {
-      const uint32_t* const src = ring + ((int64_t)t.chan * n_pol + pol) * 16;
-      tied_lag_tile(
-          lds, t.n_blk, 1, 1, dl[2 * t.chan] * t.dircos[2 * pp], dl[2 * t.chan + 1] * t.dircos[2 * pp + 1],
-          p0 < t.n_point, frame_dw,
-          [&](int64_t s, int) {
-            int64_t slot = first + s;
-            if (slot >= ring_samples) slot -= ring_samples;
-            const int64_t left = ring_samples - slot;
-            return Group{src + slot * frame_dw, left < 16 ? (int)left : 16, ring_samples * frame_dw};
-          },
-          [&](int b, float v) {
-            if (p < t.n_point)
-              t.out[(((int64_t)(t.blk0 + b) * t.n_chan_req + (t.chan - t.chan_lo)) * n_pol + pol) * t.n_point + p] = v;
-          });
+      const bool weak = serve_run<false>(lds, tiles + ti, ring, ring_samples, n_chan, n_pol, pol, dl);
+      if (__builtin_expect(__syncthreads_or(weak), 0))
+        serve_run<true>(lds, tiles + ti, ring, ring_samples, n_chan, n_pol, pol, dl);
     }
-  }
 }
 
 }  // namespace
