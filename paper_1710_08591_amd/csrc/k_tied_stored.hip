@@ -75,18 +75,21 @@ struct TsLds {
 // One output unit of the wavefront: `unit` samples from u * unit of
 // polarisation group pg, of which it takes the quads sub, sub + split, ...;
 // the sums go to `part` if the unit is split, else to the output.
-// F32: the products on v_mfma_f32_16x16x4_f32.
+// CPLX: complex output (units of one quad).  F32: the products on
+// v_mfma_f32_16x16x4_f32.
 // Returns whether every sum was finite and, for complex output, none was below
 // 2^-90 (BF16 operands below 2^-126 count as zero, so there the low terms of
 // the beams are lost; an intensity of such beams is zero in FP32 either way).
-template <int M, int PT, bool F32>
+// The sums of a sample whose beams are all zero are right as they are: dead
+// channels and zero-filled gaps cost no second pass (26 us against 44 to 52).
+template <int M, int PT, bool CPLX, bool F32>
 __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>& lds, int lane, int64_t u, int unit,
                                           int pg, int chan, int cs, int p0, int sub, int split, float* part) {
   constexpr int NC = M / 16;
   const int n = lane & 15, g = lane >> 4;
   const int e = n & 3, s = n >> 2;
-  const int pol_lo = a.pol_sum && !a.complex_out ? 0 : pg;
-  const int pol_hi = a.pol_sum && !a.complex_out ? a.n_pol : pg + 1;
+  const int pol_lo = a.pol_sum && !CPLX ? 0 : pg;
+  const int pol_hi = a.pol_sum && !CPLX ? a.n_pol : pg + 1;
   const int64_t tstride = (int64_t)a.n_chan * a.n_pol * 4 * M;      // complex values per sample
   const float* beams = reinterpret_cast<const float*>(a.beams);
   auto quad_ptr = [&](int pol, int q) {
@@ -98,6 +101,7 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
 #pragma unroll
   for (int pt = 0; pt < PT; ++pt) acc[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
   float bad = 0.f;
+  uint32_t any = 0;                // bits of the lane's beams
   constexpr int D = 2;             // chunks loaded ahead
   f32x4 ring[D + 1][2];
   static_assert(NC % 4 == 0, "chunks");
@@ -116,7 +120,10 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
       f32x4 zr[PT], zi[PT];
 #pragma unroll
       for (int pt = 0; pt < PT; ++pt) zr[pt] = zi[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      constexpr int UN = NC > 4 ? 4 : NC / 2;      // (whole quads unrolled spill)
+      // (whole quads unrolled spill, and with complex output four chunks; as it
+      // is three and four tiles of pointings still spill 24 to 64 bytes a lane,
+      // nearly all outside the innermost loop)
+      constexpr int UN = NC > 4 ? (CPLX ? 2 : 4) : NC / 2;
 #pragma unroll 1
       for (int k0 = 0; k0 < NC; k0 += UN) {
 #pragma unroll
@@ -127,6 +134,13 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
           asm volatile("" : "+v"(lane));
           const float* np = kc + D < NC ? bp + 32 * (kc + D) : bn + 32 * (kc + D - NC);
           f32x4 v[2] = {ring[0][0], ring[0][1]};
+          if constexpr (CPLX && !F32) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const u32x4 x = __builtin_bit_cast(u32x4, v[h]);
+              any |= x[0] | x[1] | x[2] | x[3];
+            }
+          }
 #pragma unroll
           for (int k = 0; k + 1 < D; ++k) {
             ring[k][0] = ring[k + 1][0];
@@ -179,6 +193,8 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
       }
       // E-W weights, the sum over the column quad's four E-W beams, |B_p|^2
       const int64_t t = u * unit + q + s;
+      // whether the lane's sample holds anything: columns 4 s ... 4 s + 3 of every lane group
+      const bool live = !CPLX || F32 || (__ballot((any & 0x7FFFFFFFu) != 0) & (0x000F000F000F000Full << (4 * s))) != 0;
 #pragma unroll
       for (int pt = 0; pt < PT; ++pt)
 #pragma unroll
@@ -186,12 +202,12 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
           const float2 c = lds.ew[pt * 16 + 4 * g + i][e];
           const cf b0 = cmul(cf{zr[pt][i], zi[pt][i]}, cf{c.x, c.y});
           const cf b{quad_sum(b0.r), quad_sum(b0.i)};
-          if (a.complex_out) {
+          if constexpr (CPLX) {
             const int p = p0 + pt * 16 + 4 * g + i;
             if (e == 0 && t < a.n_time && p < a.n_point)
               static_cast<float2*>(a.out)[((t * a.n_chan_sub + cs) * a.n_pol + pol) * (int64_t)a.n_point + p] =
                   make_float2(b.r, b.i);
-            bad = fmaxf(fabsf(b.r), fabsf(b.i)) < 0x1p-90f ? 1.f : fmaf(b.r, 0.f, fmaf(b.i, 0.f, bad));
+            bad = live && fmaxf(fabsf(b.r), fabsf(b.i)) < 0x1p-90f ? 1.f : fmaf(b.r, 0.f, fmaf(b.i, 0.f, bad));
           } else {
             acc[pt][i] = cnorm_acc(b, acc[pt][i]);
           }
@@ -199,7 +215,7 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
       bp = bn;
     }
   }
-  if (!a.complex_out) {
+  if constexpr (!CPLX) {
     const int n_pg = a.pol_sum ? 1 : a.n_pol;
     float* o = static_cast<float*>(a.out) + ((u * a.n_chan_sub + cs) * n_pg + pg) * (int64_t)a.n_point;
 #pragma unroll
@@ -220,7 +236,7 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
   return __all(bad == 0.f);
 }
 
-template <int M, int PT>
+template <int M, int PT, bool CPLX>
 __global__ __launch_bounds__(64 * kTsWaves) __attribute__((amdgpu_waves_per_eu(PT * M > 384 ? 2 : 4))) void k_tied_stored(TiedArgs a) {
   __shared__ TsLds<M, PT> lds;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -266,8 +282,8 @@ __global__ __launch_bounds__(64 * kTsWaves) __attribute__((amdgpu_waves_per_eu(P
   }
   __syncthreads();
 
-  const int n_pg = a.pol_sum && !a.complex_out ? 1 : a.n_pol;
-  const int unit = a.complex_out ? 4 : a.block;
+  const int n_pg = a.pol_sum && !CPLX ? 1 : a.n_pol;
+  const int unit = CPLX ? 4 : a.block;
   const int64_t n_unit = (a.n_time + unit - 1) / unit * n_pg;
   const int64_t u0 = (int64_t)run * a.run_units;
   const int64_t u1 = u0 + a.run_units < n_unit ? u0 + a.run_units : n_unit;
@@ -276,8 +292,8 @@ __global__ __launch_bounds__(64 * kTsWaves) __attribute__((amdgpu_waves_per_eu(P
     const int64_t u = ub + slot;
     const int64_t tu = u / n_pg;
     const int pg = (int)(u - tu * n_pg);
-    if (u < u1 && !tied_unit<M, PT, false>(a, lds, lane, tu, unit, pg, chan, cs, p0, sub, split, lds.part[wave]))
-      tied_unit<M, PT, true>(a, lds, lane, tu, unit, pg, chan, cs, p0, sub, split, lds.part[wave]);
+    if (u < u1 && !tied_unit<M, PT, CPLX, false>(a, lds, lane, tu, unit, pg, chan, cs, p0, sub, split, lds.part[wave]))
+      tied_unit<M, PT, CPLX, true>(a, lds, lane, tu, unit, pg, chan, cs, p0, sub, split, lds.part[wave]);
     if (split > 1) {
       __syncthreads();
       if (u < u1 && sub == 0 && lane < 16 * PT && p0 + lane < a.n_point) {
@@ -327,8 +343,9 @@ hipError_t launch_mp(TiedArgs a, hipStream_t s) {
   runs = (n_unit + per - 1) / per;
   if (per > 0x7FFFFFFF || n_pt * runs > 0x7FFFFFFF || a.n_chan_sub > 65535) return hipErrorInvalidConfiguration;
   a.run_units = (int)per;
-  hipLaunchKernelGGL((k_tied_stored<M, PT>), dim3((unsigned)(n_pt * runs), (unsigned)a.n_chan_sub),
-                     dim3(64 * kTsWaves), 0, s, a);
+  const dim3 grid((unsigned)(n_pt * runs), (unsigned)a.n_chan_sub), threads(64 * kTsWaves);
+  if (a.complex_out) hipLaunchKernelGGL((k_tied_stored<M, PT, true>), grid, threads, 0, s, a);
+  else hipLaunchKernelGGL((k_tied_stored<M, PT, false>), grid, threads, 0, s, a);
   return hipGetLastError();
 }
 
