@@ -18,7 +18,8 @@
 // four rows' loads are in flight: the largest value by a prefix maximum over
 // the lanes (DPP), its lowest index from the masks of the lanes that hold it
 // (one compare per beam of a lane, the rest on the scalar unit).  The four rows
-// pass through LDS, from where 16 lanes a row pick the K window beams; then
+// pass through LDS, from where 16 lanes a row pick the K window beams (more than
+// 16: one row at a time, a lane a beam); then
 // every lane runs the Newton phase for one row.  Bound by the reads: 131072
 // rows of 512 beams (268 MB) take 61 us, 4.4 TB/s; with each four rows' loads
 // waited for, a (value, index) argmax of about 120 vector instructions a row
@@ -71,9 +72,14 @@ __device__ __forceinline__ float wave_max(float v) {
 template <int PER, bool VEC, int KMAX>
 __global__ __launch_bounds__(256) void k_localize(LocArgs a) {
   constexpr int WS = KMAX + 1;                     // padded LDS row of window beams
+  // rows that pass through LDS at a time: with the wide window four would leave
+  // room for one workgroup per CU instead of two (131072 rows of 512 beams, 64 of
+  // them in the window: 153 us against 111)
+  constexpr int RB = KMAX > 16 ? 1 : 4;
+  static_assert(2 * (4 * 4 * 64 * WS + 2 * 8 * KMAX + 4 * 4 * RB * 64 * PER) <= 160 * 1024, "two workgroups per CU");
   __shared__ float win[4][64 * WS];
   __shared__ double tab[2][KMAX];                  // cos, sin of pi j/M
-  __shared__ __attribute__((aligned(16))) float rows[4][4][64 * PER];   // the four rows at hand
+  __shared__ __attribute__((aligned(16))) float rows[4][RB][64 * PER];  // the rows at hand
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int m = a.m, K = a.n_window, N = 2 * a.n - 1;
   const double inv_m = 1.0 / (double)m;
@@ -142,28 +148,32 @@ __global__ __launch_bounds__(256) void k_localize(LocArgs a) {
         if (at[i] >> l & 1) i0 = i;
       a0[r] = l * PER + i0;
       if (lane == rb + r) my_a0 = a0[r];
-      float* const x = &rows[wave][r][lane * PER];
-      if constexpr (PER >= 4) {
-#pragma unroll
-        for (int q = 0; q < PER / 4; ++q)
-          reinterpret_cast<float4*>(x)[q] = make_float4(v[r][4 * q], v[r][4 * q + 1], v[r][4 * q + 2], v[r][4 * q + 3]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < PER; ++i) x[i] = v[r][i];
-      }
     }
-    wave_lds_sync();
     // window beams A = a0 - half + jj (mod m, a power of two), jj < K
-    {
-      const int r = lane >> 4;
-      const int ar = r < 2 ? (r ? a0[1] : a0[0]) : (r == 2 ? a0[2] : a0[3]);
 #pragma unroll
-      for (int j0 = 0; j0 < KMAX; j0 += 16) {
-        const int jj = j0 + (lane & 15);
-        if (jj < K) w[(rb + r) * WS + jj] = rows[wave][r][(ar - half + jj) & (m - 1)];
+    for (int r0 = 0; r0 < 4; r0 += RB) {
+#pragma unroll
+      for (int r = r0; r < r0 + RB; ++r) {
+        float* const x = &rows[wave][r - r0][lane * PER];
+        if constexpr (PER >= 4) {
+#pragma unroll
+          for (int q = 0; q < PER / 4; ++q)
+            reinterpret_cast<float4*>(x)[q] = make_float4(v[r][4 * q], v[r][4 * q + 1], v[r][4 * q + 2], v[r][4 * q + 3]);
+        } else {
+#pragma unroll
+          for (int i = 0; i < PER; ++i) x[i] = v[r][i];
+        }
       }
+      wave_lds_sync();
+      if constexpr (RB == 4) {
+        const int r = lane >> 4, jj = lane & 15;
+        const int ar = r < 2 ? (r ? a0[1] : a0[0]) : (r == 2 ? a0[2] : a0[3]);
+        if (jj < K) w[(rb + r) * WS + jj] = rows[wave][r][(ar - half + jj) & (m - 1)];
+      } else {
+        if (lane < K) w[(rb + r0) * WS + lane] = rows[wave][0][(a0[r0] - half + lane) & (m - 1)];
+      }
+      wave_lds_sync();
     }
-    wave_lds_sync();
   }
   // ---- Newton phase: lane = row ----
   const int64_t row = row0 + lane;
