@@ -131,9 +131,12 @@ bf_status bf_plan_get_desc(const bf_plan *plan, bf_plan_desc *desc);
  * Intensities without a taper (m_ns = 2 n_ns, m_ew = 4) come from the block's
  * stacked visibilities (eq. e:b_V_delta), exact integer sums of the int4
  * samples, transformed in FP64 and rounded once to float, in plans of every
- * precision (FP16 plans of the 4 x 16 lattice keep products of the exact E-W
- * sums with two-term FP16 coefficients, FP32 sums, for short blocks).  FP16
- * and FP8 plans produce intensities only.  With a taper
+ * precision.  (FP16 plans of the 4 x 16 lattice with 32 or more channels and
+ * output polarisations, and blocks of up to 32 samples counted over the summed
+ * polarisations, keep products of the exact E-W sums with two-term FP16
+ * coefficients and FP32 sums.)  The method, and so the rounding, does not depend
+ * on the length of the call.  FP16 and FP8 plans produce intensities only.
+ * With a taper
  * (16-byte aligned), FP16 plans split the windowed E-W sums and the DFT
  * coefficients into FP16 high and low parts, accumulating in FP32; FP8 plans
  * return BF_ERR_UNSUPPORTED.  FP16 and FP8 plans need 16-byte aligned volts.

@@ -261,12 +261,15 @@ static bf_status beamform_fft_impl(const bf_plan* plan, const uint8_t* volts, in
   if (n_wg > 0x7FFFFFFFLL) return fail(BF_ERR_UNSUPPORTED, "beamform_fft: grid too large, split the call");
   hipError_t e;
   const int pol_iter = (n_pg == 1) ? d.n_pol : 1;
-  // The 4 x 16 lattice's FP16 plans keep their dense 16-point products where
-  // short blocks leave the stacked visibilities an FP64 transform per few
-  // samples: 256 channels, 2 polarisations, 1024 blocks of 16 samples 308 us
-  // against 327, 256 summed 67 against 77, blocks of 48 44 against 46; blocks of
-  // 80 128 against 124, and few tasks leave them too few wavefronts.
-  const bool dense16 = d.precision == BF_PREC_FP16_MFMA && d.n_ns == 16 && d.block <= 64 && n_wg >= 4096;
+  // The 4 x 16 lattice's FP16 plans keep their dense 16-point products where a
+  // block's samples (of the summed polarisations) are so few that the stacked
+  // visibilities' FP64 transform per block outweighs them: 256 channels and 256
+  // blocks of 16 samples 45 us against 49, 32 samples 72 against 74 (summed 71
+  // against 79); 48 samples 102 against 96, 64 samples 142 against 121.  Plans of
+  // few channels, whose calls are short, do not gain.  The choice is the plan's
+  // alone, so a stream may be cut into calls anywhere.
+  const bool dense16 = d.precision == BF_PREC_FP16_MFMA && d.n_ns == 16 && (int64_t)d.block * pol_iter <= 32 &&
+                       (int64_t)d.n_chan * n_pg >= 32;
   if (kind == BF_OUT_INTENSITY && !taper && plan->lag && !dense16) {
     fftbf::LagArgs a{};
     a.volts = reinterpret_cast<const uint32_t*>(volts);
