@@ -47,7 +47,9 @@ class HipBackend final : public fftbf::serve::Backend {
   ~HipBackend() override {
     if (copy_) (void)hipStreamSynchronize(copy_);
     if (stream_) (void)hipStreamSynchronize(stream_);
-    for (Reader& r : readers_) (void)hipEventDestroy(r.ev);
+    for (int i = 0; i < n_reads_; ++i) (void)hipEventDestroy(reads_[i].ev);
+    for (hipEvent_t ev : ev_half_)
+      if (ev) (void)hipEventDestroy(ev);
     for (int i = 0; i < kSlots; ++i) {
       if (ev_copy_[i]) (void)hipEventDestroy(ev_copy_[i]);
       if (ev_[i]) (void)hipEventDestroy(ev_[i]);
@@ -73,7 +75,8 @@ class HipBackend final : public fftbf::serve::Backend {
     max_tiles_ = max_tiles;
     hipError_t e = hipStreamCreateWithFlags(&stream_, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&copy_, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipHostMalloc(&arena_, kArenaBytes, hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostMalloc(&arena_, 2 * kHalfBytes, hipHostMallocDefault);
+    for (int i = 0; i < 2 && e == hipSuccess; ++i) e = hipEventCreateWithFlags(&ev_half_[i], hipEventDisableTiming);
     if (e == hipSuccess) e = hipMalloc(&ring_, sample_bytes() * ring_samples);
     if (e == hipSuccess) e = hipMemsetAsync(ring_, 0, sample_bytes() * ring_samples, stream_);
     if (e == hipSuccess) e = hipMalloc(&pool_, pool_bytes);
@@ -95,49 +98,58 @@ class HipBackend final : public fftbf::serve::Backend {
   size_t sample_bytes() const { return frame_bytes_ * n_chan_ * n_pol_; }
 
   // Uploads go through pinned memory on a stream of their own, which every
-  // launch waits for: a submission costs no wait, and a batch's descriptors
-  // are copied while the batch before it runs (a burst of 24 requests: 17 us
-  // per submission with a synchronous copy, 30 us between batches with the
-  // descriptors on the launch stream).
+  // launch waits for: a submission does not wait for its copy, and a batch's
+  // descriptors are copied while the batch before it runs (a burst of 24
+  // requests: 17 us per submission with a synchronous copy, 30 us between
+  // batches with the descriptors on the launch stream).  The memory has two
+  // halves in turn, and a submission that enters a half waits for the copies out
+  // of it, all issued before the other half's: it waits for a caller's long read
+  // only if more than 512 KiB of tables were submitted behind that.
   bool upload_pointings(size_t off, const double* dircos, int n_point) override {
-    const size_t bytes = sizeof(double) * 2 * n_point;
-    hipError_t e = wait_readers();
-    if (e == hipSuccess && (bytes > kArenaBytes || used_ + bytes > kArenaBytes)) {
-      e = hipStreamSynchronize(copy_);        // the arena's copies are done
+    const size_t bytes = sizeof(double) * 2 * n_point;      // 64 KiB at most (4096 pointings)
+    if (bytes > kHalfBytes) return false;
+    hipError_t e = hipSuccess;
+    if (used_ + bytes > kHalfBytes) {
+      e = hipEventRecord(ev_half_[half_], copy_);
+      half_ ^= 1;
       used_ = 0;
+      if (e == hipSuccess && second_round_) e = hipEventSynchronize(ev_half_[half_]);
+      second_round_ = true;                                 // from now on both halves have an event
     }
-    char* const dst = static_cast<char*>(pool_) + off;
-    if (e == hipSuccess && bytes > kArenaBytes) return hipMemcpy(dst, dircos, bytes, hipMemcpyHostToDevice) == hipSuccess;
+    if (e == hipSuccess) e = wait_reads();
     if (e != hipSuccess) return false;
-    std::memcpy(arena_ + used_, dircos, bytes);
-    e = hipMemcpyAsync(dst, arena_ + used_, bytes, hipMemcpyHostToDevice, copy_);
+    char* const from = arena_ + half_ * kHalfBytes + used_;
+    std::memcpy(from, dircos, bytes);
+    e = hipMemcpyAsync(static_cast<char*>(pool_) + off, from, bytes, hipMemcpyHostToDevice, copy_);
     used_ += bytes;
     return e == hipSuccess;
   }
 
   // A caller's stream now reads a request's outputs.  Memory that is given
   // back while it does must not be written before that read: once a release
-  // follows, the next upload or launch waits for it.
+  // follows, the next upload or launch waits for it on the device.  Every read
+  // has an event of its own until it is over or waited for; if all are taken,
+  // the uploads wait for the one that was recorded first.
   hipError_t reads(hipStream_t s) {
-    for (Reader& r : readers_)
-      if (r.s == s) {
-        if (r.state != kReleased) r.state = kReading;   // the later record covers the earlier reads
-        return hipEventRecord(r.ev, s);
-      }
-    if (readers_.size() >= kMaxReaders) return hipStreamSynchronize(s);
-    Reader r{s, nullptr, kReading};
-    hipError_t e = hipEventCreateWithFlags(&r.ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventRecord(r.ev, s);
-    if (e != hipSuccess) {
-      if (r.ev) (void)hipEventDestroy(r.ev);
-      return e;
+    int k = 0;
+    while (k < n_reads_ && reads_[k].state != kIdle && hipEventQuery(reads_[k].ev) != hipSuccess) ++k;
+    if (k == kMaxReads) {
+      k = next_read_;
+      next_read_ = (next_read_ + 1) % kMaxReads;
+      const hipError_t e = hipStreamWaitEvent(copy_, reads_[k].ev, 0);
+      if (e != hipSuccess) return e;
+    } else if (k == n_reads_) {
+      const hipError_t e = hipEventCreateWithFlags(&reads_[k].ev, hipEventDisableTiming);
+      if (e != hipSuccess) return e;
+      ++n_reads_;
     }
-    readers_.push_back(r);
-    return hipSuccess;
+    const hipError_t e = hipEventRecord(reads_[k].ev, s);
+    reads_[k].state = e == hipSuccess ? kReading : kIdle;
+    return e;
   }
   void released() {
-    for (Reader& r : readers_)
-      if (r.state == kReading) r.state = kReleased;
+    for (int i = 0; i < n_reads_; ++i)
+      if (reads_[i].state == kReading) reads_[i].state = kReleased;
   }
 
   int64_t launch(const std::vector<Tile>& tiles, const std::vector<const Request*>& reqs) override {
@@ -162,7 +174,7 @@ class HipBackend final : public fftbf::serve::Backend {
       d.pad = 0;
     }
     FFTBF_TRACE("bf_server batch launch");
-    hipError_t e = wait_readers();
+    hipError_t e = wait_reads();
     if (e == hipSuccess) e = hipMemcpyAsync(dev_[slot], h, sizeof(fftbf::ServeTile) * n, hipMemcpyHostToDevice, copy_);
     if (e == hipSuccess) e = hipEventRecord(ev_copy_[slot], copy_);
     if (e == hipSuccess) e = hipStreamWaitEvent(stream_, ev_copy_[slot], 0);
@@ -196,27 +208,31 @@ class HipBackend final : public fftbf::serve::Backend {
   hipError_t err_ = hipSuccess;
 
  private:
-  static constexpr size_t kArenaBytes = size_t(1) << 20, kMaxReaders = 16;
+  static constexpr size_t kHalfBytes = size_t(1) << 19;
+  static constexpr int kMaxReads = 64;
   enum ReadState { kIdle, kReading, kReleased };
-  struct Reader {
-    hipStream_t s;
+  struct Read {
     hipEvent_t ev;
     ReadState state;
   };
-  hipError_t wait_readers() {
-    for (Reader& r : readers_) {
-      if (r.state != kReleased) continue;
-      const hipError_t e = hipStreamWaitEvent(copy_, r.ev, 0);
+  hipError_t wait_reads() {
+    for (int i = 0; i < n_reads_; ++i) {
+      if (reads_[i].state != kReleased) continue;
+      const hipError_t e = hipStreamWaitEvent(copy_, reads_[i].ev, 0);
       if (e != hipSuccess) return e;
-      r.state = kIdle;
+      reads_[i].state = kIdle;
     }
     return hipSuccess;
   }
 
   hipStream_t copy_ = nullptr;               // uploads
-  char* arena_ = nullptr;                    // pinned staging of pointing tables
-  size_t used_ = 0;
-  std::vector<Reader> readers_;              // callers' streams that copied results
+  char* arena_ = nullptr;                    // pinned staging of pointing tables, two halves
+  size_t used_ = 0;                          // bytes of the half in use
+  int half_ = 0;
+  bool second_round_ = false;
+  hipEvent_t ev_half_[2] = {};               // the copies out of each half
+  Read reads_[kMaxReads] = {};               // copies of results on callers' streams
+  int n_reads_ = 0, next_read_ = 0;
   hipEvent_t ev_copy_[kSlots] = {};
   int n_chan_ = 0, n_pol_ = 0, max_tiles_ = 0;
   int64_t ring_samples_ = 0, count_ = 0;
