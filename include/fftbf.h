@@ -412,7 +412,9 @@ bf_status bf_server_poll(bf_server *srv, int64_t id, double *latency_s);
 /* Device pointer to a finished request's intensities
  * float [n_time/16][n_chan][n_pol][n_point], valid until released. */
 bf_status bf_server_result(bf_server *srv, int64_t id, float **out, int64_t *n_floats);
-/* Copy a finished result into caller device memory dst on stream. */
+/* Copy a finished result into caller device memory dst on stream.  The request
+ * may be released at once.  On a stream under capture the copy is recorded: it
+ * reads at each replay, so keep the request until the last one is over. */
 bf_status bf_server_copy_result(bf_server *srv, int64_t id, float *dst, void *stream);
 /* Return a finished, cancelled or evicted request's memory to the pool
  * (BF_ERR_NOT_READY while its tiles are still on the device). */

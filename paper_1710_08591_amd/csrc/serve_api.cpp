@@ -131,6 +131,10 @@ class HipBackend final : public fftbf::serve::Backend {
   // has an event of its own until it is over or waited for; if all are taken,
   // the uploads wait for the one that was recorded first.
   hipError_t reads(hipStream_t s) {
+    // A copy that is recorded into a graph reads when the graph runs, and an
+    // event of a capture would draw the upload stream into it.
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone) return hipSuccess;
     int k = 0;
     while (k < n_reads_ && reads_[k].state != kIdle && hipEventQuery(reads_[k].ev) != hipSuccess) ++k;
     if (k == kMaxReads) {
