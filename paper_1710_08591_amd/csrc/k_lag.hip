@@ -23,18 +23,19 @@
 // E-W beam at n = 256, 136 without the tiles' empty corners.
 //
 // Per 16 samples of a 4 x 256 lattice and polarisation: 640 matrix products
-// (16 cycles each), 200 other vector instructions per sample against 836 of
+// (16 cycles each), 158 other vector instructions per sample against 836 of
 // an FP32 transform per sample.  MI355X, 4 x 256, 2 polarisations, 256
 // channels, 16384 samples, 16-sample blocks, 256 of 512 beams kept:
 // 10.0 -> 6.9 ms (FP32 transform per sample -> this); FP16 matrix cores per
 // sample 9.1 ms.  4 x 128 (8192 samples) 2.13 -> 1.37, 4 x 64 2.03 -> 1.25,
 // 4 x 32 0.93 -> 0.64, 4 x 16 0.53 -> 0.37 ms (256 channels, 2
 // polarisations; matrix cores per sample at 4 x 16: FP16 0.38, FP8 0.50 ms).
-// Bound at n = 256: power.  The clock holds 1.9 GHz on random voltages, the
-// matrix cores are busy 37 % and the vector units 40 % of the cycles, and
-// variants with 25 % fewer vector instructions, with two to four wavefronts
-// per SIMD, with half the LDS reads or with reads issued ahead all run
-// within 3 % of each other.
+// Bound at n = 256: 640 cycles of products and 632 of vector issue a frame would
+// be 4.9 ms one strictly after the other at the 2.13 GHz that the clock holds on
+// random voltages.  The rest is waiting (37 % of the wavefronts' cycles): two
+// barriers bracket each step and two workgroups share a CU.  Variants with 25 %
+// fewer vector instructions, with two to four wavefronts per SIMD, with half the
+// LDS reads or with reads issued ahead all run within 3 % of each other.
 #include <type_traits>
 
 #include "dev_bytes.h"
@@ -380,7 +381,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     // task without signal (R_0 = 0) is zero, its rounding noise is not stored.
     float norm1, norm2;
     {
-      const sum_t p1 = own[ps * N], p2 = own[512 + ps * N];
+      sum_t p1 = own[ps * N], p2 = own[512 + ps * N];
       sum_t ur[8], ui[8], vr[8], vi[8];
       const sum_t* const up = own + ps * N + l;
       const sum_t* const down = own + ps * N - l;
@@ -392,15 +393,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         vr[i] = r[512];
         vi[i] = r[768];
       }
-      int sh = 0;
-      if (p1 != 0 && p2 != 0) sh = __builtin_amdgcn_frexp_exp((double)p1) - __builtin_amdgcn_frexp_exp((double)p2);
-      if (sh >= -8 && sh <= 8) sh = 0;
-      norm1 = p1 != 0 ? p.norm : 0.f;
-      norm2 = p2 != 0 ? ldexpf(p.norm, -sh) : 0.f;
-      if constexpr (PL == 64) {
-        norm1 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, norm1)));
-        norm2 = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, norm2)));
+      int sh;
+      if constexpr (LONG) {
+        sh = __builtin_amdgcn_frexp_exp(p1) - __builtin_amdgcn_frexp_exp(p2);
+      } else {
+        if constexpr (PL == 64) {            // one task a wavefront: on the scalar unit
+          p1 = __builtin_amdgcn_readfirstlane(p1);
+          p2 = __builtin_amdgcn_readfirstlane(p2);
+        }
+        sh = __builtin_clz(p2 | 1) - __builtin_clz(p1 | 1);
       }
+      if (p1 == 0 || p2 == 0 || (sh >= -8 && sh <= 8)) sh = 0;
+      norm1 = p1 != 0 ? p.norm : 0.f;
+      norm2 = p2 != 0 ? p.norm : 0.f;
       if (!__any(sh != 0)) {
 #pragma unroll
         for (int i = 0; i < 8; ++i)
@@ -411,6 +416,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
           const double a = (double)ur[i], b = (double)ui[i], c = ldexp((double)vr[i], sh), d = ldexp((double)vi[i], sh);
           z[i] = i < 4 ? cd{a - d, b + c} : cd{a + d, c - b};
         }
+        norm2 = ldexpf(norm2, -sh);
       }
       if (l == 0) z[4] = cd{0.0, 0.0};                   // lag N: not formed
     }
