@@ -283,6 +283,8 @@ bf_status bf_accumulate_intensity(const void *z, int64_t n_time, int64_t n_serie
  *
  * The weights are generated in FP64 on the device at creation and rounded to
  * FP32 (owned by the regrid object); the contraction has FP32 operands and sums.
+ * Dense weights take six bytes each, n_chan x n_target x m_ns of them, with
+ * n_target rounded up to 64 or to a multiple of 256.
  */
 typedef struct bf_regrid bf_regrid;
 

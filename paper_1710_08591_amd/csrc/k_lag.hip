@@ -23,15 +23,15 @@
 // E-W beam at n = 256, 136 without the tiles' empty corners.
 //
 // Per 16 samples of a 4 x 256 lattice and polarisation: 640 matrix products
-// (16 cycles each), 158 other vector instructions per sample against 836 of
+// (16 cycles each), 159 other vector instructions per sample against 836 of
 // an FP32 transform per sample.  MI355X, 4 x 256, 2 polarisations, 256
 // channels, 16384 samples, 16-sample blocks, 256 of 512 beams kept:
 // 10.0 -> 6.9 ms (FP32 transform per sample -> this); FP16 matrix cores per
 // sample 9.1 ms.  4 x 128 (8192 samples) 2.13 -> 1.37, 4 x 64 2.03 -> 1.25,
 // 4 x 32 0.93 -> 0.64, 4 x 16 0.53 -> 0.37 ms (256 channels, 2
 // polarisations; matrix cores per sample at 4 x 16: FP16 0.38, FP8 0.50 ms).
-// Bound at n = 256: 640 cycles of products and 632 of vector issue a frame would
-// be 4.9 ms one strictly after the other at the 2.13 GHz that the clock holds on
+// Bound at n = 256: 640 cycles of products and 636 of vector issue a frame would
+// be 5.0 ms one strictly after the other at the 2.1 GHz that the clock holds on
 // random voltages.  The rest is waiting (37 % of the wavefronts' cycles): two
 // barriers bracket each step and two workgroups share a CU.  Variants with 25 %
 // fewer vector instructions, with two to four wavefronts per SIMD, with half the

@@ -11,7 +11,8 @@
 //
 // The weights are generated once in FP64 on the device (the removable
 // singularity at integer y takes its limit (2n-1)/M), rounded to FP32 and
-// stored as three BF16 terms each (dev_bf16.h).  The contraction
+// stored as three BF16 terms each (dev_bf16.h): six bytes a weight, where FP32
+// would take four, so that no workgroup splits them again.  The contraction
 // Out[row][target] = sum_A I[row][A] W[target][A] (rows = (block, polarisation,
 // E-W beam) of one channel) runs on v_mfma_f32_16x16x32_bf16, six products for
 // one in FP32.  A workgroup of W wavefronts owns 256 targets (TG = 2 groups of

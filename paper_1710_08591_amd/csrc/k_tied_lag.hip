@@ -70,6 +70,8 @@ struct Group {
 // not pay for it beyond the comparison (64 pointings, 256 channels, 16384 samples
 // 159 -> 162 us); without noise the same call takes 496 us (818 by FFT beams per
 // sample).
+// (The pass for these outputs spills: 160 to 200 bytes a lane.  The ordinary pass
+// keeps to its registers.)
 constexpr float kWeak = 0x1p-13f;
 constexpr double kLowUnit = 2147483648.0;  // 2^31
 

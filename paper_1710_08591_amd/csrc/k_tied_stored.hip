@@ -17,7 +17,7 @@
 // and reads, splits and multiplies each beam once for all PT tiles.
 //
 // 4 x 64, 32 channels, 2 polarisations, 2048 samples, 48 pointings: 537 MB of
-// beams in 178 us (3.0 TB/s); the same contraction on v_mfma_f32_16x16x4_f32,
+// beams in 168 us (3.2 TB/s); the same contraction on v_mfma_f32_16x16x4_f32,
 // one tile of 16 pointings per workgroup, took 404 us, bound by the FP32
 // matrix rate (179 us) and by reading the beams three times.  The products
 // take about 70 us here and the reads about 110: neither fills its unit, the
