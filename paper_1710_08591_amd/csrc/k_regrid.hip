@@ -171,7 +171,7 @@ __device__ __forceinline__ void regrid_f32(const float* const (&arow)[RT], const
 // E-W axis padded to 8 beams -- the 8 E-W rows of each (block, pol group)
 // are combined with the E-W weights in the epilogue.
 template <int W, int RT, int TG, int KS, bool ONE, bool EW2D>
-__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(TG == 1 || ONE ? 4 : W / 4))) void k_regrid(RegridArgs a) {
+__global__ __launch_bounds__(64 * W) __attribute__((amdgpu_waves_per_eu(KS == 2 ? 3 : TG == 1 || ONE ? 4 : W / 4))) void k_regrid(RegridArgs a) {
   constexpr int NT = TG == 2 ? 8 : 4;     // target tiles per wavefront
   constexpr int TILES = NT * TG;          // target tiles per workgroup
   constexpr int RG = W / TG;              // groups of wavefronts along the rows
