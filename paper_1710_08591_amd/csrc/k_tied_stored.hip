@@ -120,10 +120,11 @@ __device__ __forceinline__ bool tied_unit(const TiedArgs& a, const TsLds<M, PT>&
       f32x4 zr[PT], zi[PT];
 #pragma unroll
       for (int pt = 0; pt < PT; ++pt) zr[pt] = zi[pt] = f32x4{0.f, 0.f, 0.f, 0.f};
-      // (whole quads unrolled spill, and with complex output four chunks; as it
+      // (whole quads unrolled spill where four wavefronts share a SIMD, and with
+      // complex output four chunks are slower as well; as it
       // is three and four tiles of pointings still spill 24 to 64 bytes a lane,
       // nearly all outside the innermost loop)
-      constexpr int UN = NC > 4 ? (CPLX ? 2 : 4) : NC / 2;
+      constexpr int UN = NC > 4 ? (CPLX ? 2 : PT * M > 384 ? 8 : 4) : NC / 2;
 #pragma unroll 1
       for (int k0 = 0; k0 < NC; k0 += UN) {
 #pragma unroll
